@@ -37,8 +37,9 @@
 //     XOR-swizzled by 16-byte granule in LDS and V rows by 64-byte segment, so that the
 //     lanes of an operand read hit distinct banks.
 //   * Scores stay raw until one FMA applies sm_scale*log2(e) and subtracts the running
-//     max before v_exp_f32.  A row's reference max is only raised when a tile exceeds it
-//     by more than kRescaleSlack, so the O rescale is skipped on almost every tile.
+//     max before v_exp_f32.  A row's reference is the maximum of its first tile and is only
+//     raised when a tile's weights outgrow it by far (kTileSumMax), so later tiles need no
+//     maximum and the O rescale is skipped on almost every one.
 //   * Causal masking is applied only on tiles that cross the diagonal.  On the last
 //     tile, V operands of key slots at or beyond the task's length are zeroed in
 //     registers, so NaN/Inf garbage in unused pool slots can never reach the output.
@@ -86,6 +87,11 @@ typedef __attribute__((address_space(1))) void glb_void;
 __device__ __forceinline__ void dma16_lane(const void* src, uint8_t* lds) {
   __builtin_amdgcn_global_load_lds((glb_void*)src, (lds_void*)lds, 16, 0, 0);
 }
+
+// A tile's weights are kept as evaluated against the row's reference unless their sum
+// exceeds this: weights then stay below 2^30, and the sums of 2^31 keys times values of up
+// to 2^60 stay inside fp32's range.
+constexpr float kTileSumMax = 1073741824.0f;  // 2^30
 
 // Physical position of 16-byte granule g of K tile row r.
 template <int D>
@@ -154,6 +160,14 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 __device__ __forceinline__ uint2 read_tr(const uint8_t* p) {
   const i16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p);
   return __builtin_bit_cast(uint2, v);
+}
+
+// The lane index, computed where it is used: the empty asm keeps it, and everything derived
+// from it, from being hoisted and held in registers across the tile walk.
+__device__ __forceinline__ int fresh_lane() {
+  int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  asm volatile("" : "+v"(l));
+  return l;
 }
 
 // Compile-time loops: f(std::integral_constant<int, i>) for i in [B, E).
@@ -288,8 +302,7 @@ void extend_attn_kernel(ExtendArgs a) {
     // across it they were spilled, and every reload drained the prefetch queue.
     const uint8_t* new_base = reinterpret_cast<const uint8_t*>(rows + new_row0 * D);
     const uint8_t* page_base = pool + blk;
-    int ln = lane;  // lane constants too are recomputed here rather than kept live
-    asm volatile("" : "+v"(ln));
+    const int ln = fresh_lane();  // lane constants too are recomputed rather than kept live
 #pragma unroll
     for (int i = 0; i < S::kDma; ++i) {
       const int r = 8 * wave + i * S::kRowsPerDma + ln / S::kNG;  // tile row
@@ -318,10 +331,11 @@ void extend_attn_kernel(ExtendArgs a) {
     const uint8_t* base =
         reinterpret_cast<const uint8_t*>(rows + (new_row0 + (int64_t)(t0 - P) * a.num_kv_heads) * D);
     const int bytes = (int)((n - 1) * new_stride) + S::kRowBytes;  // rows past n read as 0
+    const int ln = fresh_lane();
 #pragma unroll
     for (int i = 0; i < S::kDma; ++i) {
-      const int r = 8 * wave + i * S::kRowsPerDma + lane / S::kNG;  // tile row
-      const int p = lane % S::kNG;
+      const int r = 8 * wave + i * S::kRowsPerDma + ln / S::kNG;  // tile row
+      const int p = ln % S::kNG;
       const int g = is_v ? (p ^ (vseg<D>(r) << 2)) : kswz<D>(r, p);  // logical granule
       dma16(base, bytes, (uint32_t)(r * (int)new_stride + g * 16), buf + lds_row0 + i * 1024);
     }
@@ -416,7 +430,7 @@ void extend_attn_kernel(ExtendArgs a) {
   for (int t = 0; t < kDT; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[t][e] = 0.0f;
-  float m_ref = kNoMax, l_part = 0.0f, l_exact = 0.0f;
+  float m_ref = kNoMax, negm = -kNoMax, l_part = 0.0f, l_exact = 0.0f;
   f32x16 sa[2], sb[2];  // S of two consecutive tiles (the one in softmax, the next one)
   u32x4 pa[4], pb[4];   // bf16 probabilities of two consecutive tiles, 16-key chunks
 
@@ -457,16 +471,47 @@ void extend_attn_kernel(ExtendArgs a) {
     }
   };
 
-  auto rescale = [&](float alpha) {
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-#pragma unroll
-      for (int t = 0; t < kDT; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) o[t][e] *= alpha;
-    }
-  };
-
   constexpr int kAhead = 3;  // operand reads in flight ahead of the MFMAs
+
+  // Raises the reference of the rows whose tile sum is not below kTileSumMax to the tile's
+  // maximum, rescales what they accumulated and evaluates the tile again.  Rows below it
+  // keep their reference (and get the same weights and sums again), so a row's result does
+  // not depend on the other rows of the wave.  Lanes l and l^32 hold one row: either's sum
+  // counts.
+  auto redo = [&](const f32x16(&s)[2], u32x4(&p)[4], float& lt, float& le)
+      __attribute__((always_inline)) {
+    float t0, t1;
+    lane_pair(lt, t0, t1);
+    const bool over = !(t0 <= kTileSumMax) || !(t1 <= kTileSumMax);
+    float mt = s[0][0];
+#pragma unroll
+    for (int f = 1; f < 32; ++f) mt = max3(mt, s[f >> 4][f & 15], s[f >> 4][f & 15]);
+    float x0, x1;
+    lane_pair(mt, x0, x1);
+    mt = max3(x0, x1, x1) * csc;
+    const float m_new = over && mt > m_ref ? mt : m_ref;
+    const float alpha = fast_exp2(m_ref - m_new);
+    m_ref = m_new;
+    negm = -m_new;
+    l_part *= alpha;
+    l_exact *= alpha;
+#pragma unroll
+    for (int t = 0; t < kDT; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[t][e] *= alpha;
+    float lw[2] = {0.0f, 0.0f}, lx[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float p0 = fast_exp2(fmaf(s[i >> 3][2 * (i & 7)], csc, negm));
+      const float p1 = fast_exp2(fmaf(s[i >> 3][2 * (i & 7) + 1], csc, negm));
+      const uint32_t w = pack_bf16x2(p0, p1);
+      p[i / 4][i % 4] = w;
+      lw[i % 2] = add_bf16x2(w, lw[i % 2]);
+      lx[i % 2] += p0 + p1;
+    }
+    lt = lw[0] + lw[1];
+    le = lx[0] + lx[1];
+  };
 
   // ---- one pipeline step, scheduled by hand -------------------------------------------
   // The softmax of tile s into pcur (after the causal mask when kDiag), interleaved with
@@ -477,9 +522,21 @@ void extend_attn_kernel(ExtendArgs a) {
   // (head-dim chunk cc = js / 2, key block st = js % 2).  Slot m issues the operand read of
   // MFMA m + kAhead, MFMA m and its
   // share of the softmax's vector instructions; a scheduling barrier closes each slot,
-  // so the instructions issue in this order and every MFMA's 32 cycles hide about four
-  // vector instructions.  Returns the accumulator rescale factor (1 unless the row's
-  // reference max was raised), which the caller applies once the P.V MFMAs are issued.
+  // so the instructions issue in this order and every MFMA's 32 cycles hide about three
+  // vector instructions.
+  //
+  // Only the first tile (no P.V) takes its maximum before its exponentials.  Every later
+  // tile evaluates them against the reference the row already has and is checked
+  // afterwards, by its row sum: below kTileSumMax no weight came near the range of bf16 or
+  // fp32, and being far above 1 costs no precision in either.  A row whose sum is not below
+  // it (or is NaN) has its reference raised to the tile's maximum and the tile evaluated
+  // again (`redo`).  That takes 19 v_max3, the lane exchange, the reference update and its
+  // exponential out of every tile's 129 vector instructions, the maximum out of the chain
+  // from S to P, and every spill out of the plain kernel (it held 45-50 spilled VGPRs).  The
+  // kernel is bound by vector issue and by the card's power limit (the same launch over
+  // zeros runs 1.3x faster), so fewer instructions help twice: 64 tasks of 2k-16k keys and
+  // 64-2,048 new tokens (28 / 4 heads, d = 128) 4.06 -> 3.88 ms, 16 re-prefills of 2k-16k
+  // 9.98 -> 9.37 ms, image-sized extends with the log-sum-exp 6.71 -> 6.21 ms.
   //
   // The operand reads of the next step's first kAhead MFMAs (P.V of this step's tile,
   // from vb_next) are issued in this step's last slots, into pre_next, before the barrier
@@ -488,14 +545,14 @@ void extend_attn_kernel(ExtendArgs a) {
   auto block = [&](auto pv_tag, auto diag_tag, int kt, f32x16(&s)[2], u32x4(&pcur)[4],
                    const u32x4(&pprev)[4], const uint8_t* vb, const uint8_t* kb,
                    f32x16(&sn)[2], const u32x4(&pre)[kAhead], const uint8_t* vb_next,
-                   u32x4(&pre_next)[kAhead]) -> float {
+                   u32x4(&pre_next)[kAhead]) __attribute__((always_inline)) {
     constexpr bool kPV = decltype(pv_tag)::value;
     constexpr bool kDiag = decltype(diag_tag)::value;
     constexpr int nS = 2 * kDC, nPV = 4 * kDT;
     constexpr int nm = kPV ? nS + nPV : nS;
     constexpr int nMask = kDiag ? 32 : 0;
     constexpr int kPerGroup = kLse ? 14 : 12;  // vector ops per 4 probabilities
-    constexpr int kHead = 23;                  // max, exchange, reference update
+    constexpr int kHead = kPV ? 0 : 22;        // first tile: max, exchange, reference
     constexpr int nOps = nMask + kHead + 8 * kPerGroup + 1;
     const int kbase = kt * 64 + 8 * h;
     const f32x16 zero16 = {};
@@ -539,11 +596,10 @@ void extend_attn_kernel(ExtendArgs a) {
     };
 
     // softmax state
-    float mc[4], mt = 0.0f, m_new = 0.0f, alpha = 1.0f, negm = 0.0f;
+    float mc[4], mt = 0.0f;
     float x[32], pr[32];
     uint32_t w[16];
-    // row sums of the tile: two chains, the first continuing the rescaled running sum
-    float lt[2], le[2];
+    float lt[2], le[2];  // row sums of the tile, in two chains
     auto E = [&](int f) -> float { return s[f >> 4][f & 15]; };
     // vector op k of the softmax
     auto op = [&](auto k_tag) {
@@ -552,29 +608,29 @@ void extend_attn_kernel(ExtendArgs a) {
         constexpr int st = k >> 4, e = k & 15;
         constexpr int off = 32 * st + 16 * (e >> 3) + (e & 7);
         if (kbase + off > lim) s[st][e] = -INFINITY;
-      } else if constexpr (k - nMask < 16) {  // four partial max chains of 8 scores
-        constexpr int kk = k - nMask, c = kk % 4, u = kk / 4, f = 8 * c;
-        if constexpr (u == 0) mc[c] = max3(E(f), E(f + 1), E(f + 2));
-        if constexpr (u == 1) mc[c] = max3(mc[c], E(f + 3), E(f + 4));
-        if constexpr (u == 2) mc[c] = max3(mc[c], E(f + 5), E(f + 6));
-        if constexpr (u == 3) mc[c] = max3(mc[c], E(f + 7), E(f + 7));
-      } else if constexpr (k - nMask == 16) {
-        mt = max3(mc[0], mc[1], mc[2]);
-      } else if constexpr (k - nMask == 17) {
-        mt = max3(mt, mc[3], mc[3]);
-      } else if constexpr (k - nMask == 18) {
-        float x0, x1;
-        lane_pair(mt, x0, x1);
-        mt = max3(x0, x1, x1);
-      } else if constexpr (k - nMask == 19) {
-        mt *= csc;
-      } else if constexpr (k - nMask == 20) {
-        m_new = mt > m_ref + kRescaleSlack ? mt : m_ref;
-      } else if constexpr (k - nMask == 21) {
-        alpha = fast_exp2(m_ref - m_new);
-      } else if constexpr (k - nMask == 22) {
-        negm = -m_new;
-        m_ref = m_new;
+      } else if constexpr (k - nMask < kHead) {
+        constexpr int r = k - nMask;
+        if constexpr (r < 16) {  // four partial max chains of 8 scores
+          constexpr int c = r % 4, u = r / 4, f = 8 * c;
+          if constexpr (u == 0) mc[c] = max3(E(f), E(f + 1), E(f + 2));
+          if constexpr (u == 1) mc[c] = max3(mc[c], E(f + 3), E(f + 4));
+          if constexpr (u == 2) mc[c] = max3(mc[c], E(f + 5), E(f + 6));
+          if constexpr (u == 3) mc[c] = max3(mc[c], E(f + 7), E(f + 7));
+        } else if constexpr (r == 16) {
+          mt = max3(mc[0], mc[1], mc[2]);
+        } else if constexpr (r == 17) {
+          mt = max3(mt, mc[3], mc[3]);
+        } else if constexpr (r == 18) {
+          float x0, x1;
+          lane_pair(mt, x0, x1);
+          mt = max3(x0, x1, x1);
+        } else if constexpr (r == 19) {
+          mt *= csc;
+        } else if constexpr (r == 20) {
+          m_ref = mt > kNoMax ? mt : kNoMax;
+        } else {
+          negm = -m_ref;
+        }
       } else if constexpr (k - nMask < kHead + 8 * kPerGroup) {
         constexpr int kk = k - nMask - kHead, g = kk / kPerGroup, r = kk % kPerGroup;
         if constexpr (r < 4) {
@@ -594,23 +650,20 @@ void extend_attn_kernel(ExtendArgs a) {
             // compiler would otherwise sink them to where the next step first reads them
             asm volatile("" ::"v"(w[i]));
           } else if constexpr (kind == 1) {
-            if constexpr (i == 0) le[0] = fmaf(l_exact, alpha, pr[0] + pr[1]);
-            else if constexpr (i == 1) le[1] = pr[2] + pr[3];
+            if constexpr (i < 2) le[i] = pr[2 * i] + pr[2 * i + 1];
             else le[i % 2] += pr[2 * i] + pr[2 * i + 1];
           } else {
-            if constexpr (i == 0) lt[0] = add_bf16x2(w[0], l_part * alpha);
-            else if constexpr (i == 1) lt[1] = add_bf16x2(w[1], 0.0f);
-            else lt[i % 2] = add_bf16x2(w[i], lt[i % 2]);
+            lt[i % 2] = add_bf16x2(w[i], i < 2 ? 0.0f : lt[i % 2]);
           }
         }
       } else {
-        l_part = lt[0] + lt[1];
-        asm volatile("" ::"v"(l_part));
+        lt[0] += lt[1];
+        asm volatile("" ::"v"(lt[0]));
         if constexpr (kLse) {
-          l_exact = le[0] + le[1];
+          le[0] += le[1];
           // like the words above: without it the exact sums (and every probability they
           // read) would be sunk into the next step, where l_exact is next used
-          asm volatile("" ::"v"(l_exact));
+          asm volatile("" ::"v"(le[0]));
         }
       }
     };
@@ -624,7 +677,12 @@ void extend_attn_kernel(ExtendArgs a) {
       static_for_range<lo, hi>([&](auto k) { op(k); });
       __builtin_amdgcn_sched_barrier(0);
     });
-    return alpha;
+    if constexpr (kPV) {
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(lt[0] <= kTileSumMax)) != 0, 0))
+        redo(s, pcur, lt[0], le[0]);
+    }
+    l_part += lt[0];
+    if constexpr (kLse) l_exact += le[0];
   };
 
   // A wave whose 32 rows all lie past the block's tokens (the last, partial block of a
@@ -659,16 +717,12 @@ void extend_attn_kernel(ExtendArgs a) {
 
   // ---- iteration 0: softmax(0) with S(1) ---------------------------------------------
   u32x4 pre_a[kAhead], pre_b[kAhead];  // first operands of odd / even iterations
-  {
-    float alpha;
-    if (tbase >= n_full)
-      alpha = block(std::false_type(), std::true_type(), tbase, sa, pa, pb, v_lds0, k_lds1, sb,
-                    pre_b, v_lds0, pre_a);
-    else
-      alpha = block(std::false_type(), std::false_type(), tbase, sa, pa, pb, v_lds0, k_lds1, sb,
-                    pre_b, v_lds0, pre_a);
-    rescale(alpha);
-  }
+  if (tbase >= n_full)
+    block(std::false_type(), std::true_type(), tbase, sa, pa, pb, v_lds0, k_lds1, sb, pre_b,
+          v_lds0, pre_a);
+  else
+    block(std::false_type(), std::false_type(), tbase, sa, pa, pb, v_lds0, k_lds1, sb, pre_b,
+          v_lds0, pre_a);
   wait_vmem<S::kGroup + S::kDma>();  // V(1) and K(2) landed
   tile_barrier();
   stream(k_lds1, v_lds3, 5, 3, fuse);
@@ -682,11 +736,9 @@ void extend_attn_kernel(ExtendArgs a) {
                   const uint8_t* vb_next, f32x16(&s)[2], f32x16(&sn)[2],
                   const u32x4(&pprev)[4], u32x4(&pcur)[4], const u32x4(&pre)[kAhead],
                   u32x4(&pre_next)[kAhead]) __attribute__((always_inline)) {
-    const float alpha = block(std::true_type(), diag_tag, tbase + i, s, pcur, pprev, vb, kb, sn,
-                              pre, vb_next, pre_next);
+    block(std::true_type(), diag_tag, tbase + i, s, pcur, pprev, vb, kb, sn, pre, vb_next, pre_next);
     // the page ids of the next loads, fetched now so that the barrier hides their latency
     const PageRef kpg = page_ref(i + 5), vpg = page_ref(i + 3);
-    rescale(alpha);
     wait_vmem<S::kGroup + S::kDma>();  // V(i+1) and K(i+2) landed
     tile_barrier();
     stream_pages(kb, vb, i + 5, i + 3, kpg, vpg, fuse_tag);

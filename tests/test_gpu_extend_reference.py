@@ -1,0 +1,82 @@
+"""Rows whose score scale jumps after their first key tile (needs an MI355X).
+
+The extend kernel takes a row's softmax reference from its first 64-key tile and raises it
+only when a later tile's weights outgrow it by far.  Here single keys of later tiles are
+scaled so that the scores jump by hundreds (base 2), up and down, in some rows of a wave and
+not in others: in unmasked tiles, on the diagonal, in the first and later chunks of a
+split-KV call, and through the fused append.  A softmax over such scores is close to one-hot
+and its error is that of bf16 weights and outputs, so the library's usual bounds hold.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_10402_amd as tide
+from gpu_harness import assert_close, assert_lse, host_f64, log
+
+pytestmark = pytest.mark.gpu
+
+
+def build(hq, hkv, d, prefix, extend, scaled, seed, bad=None):
+    """One task; keys `scaled` = {position: factor}; `bad` = (position, value) sets a key."""
+    g = torch.Generator().manual_seed(seed)
+    n = prefix + extend
+    q = torch.randn((extend, hq, d), generator=g).bfloat16()
+    k = torch.randn((n, hkv, d), generator=g)
+    for pos, f in scaled.items():
+        k[pos] *= f
+    if bad:
+        k[bad[0]] = bad[1]
+    k = k.bfloat16()
+    v = torch.randn((n, hkv, d), generator=g).bfloat16()
+    x = torch.einsum("tghd,pgd->tghp", q.double().view(extend, hkv, hq // hkv, d), k.double()) / d ** 0.5
+    seen = torch.arange(n) <= torch.arange(prefix, n)[:, None]
+    x = x.masked_fill(~seen[:, None, None, :], -np.inf)
+    w = torch.softmax(x, -1)
+    ref = torch.einsum("tghp,pgd->tghd", w, v.double()).reshape(extend, hq, d).numpy()
+    lse = torch.logsumexp(x, -1).reshape(extend, hq).numpy()
+    pages = -(-n // 16)
+    bt = np.random.default_rng(seed).permutation(pages).astype(np.int32).reshape(1, -1)
+    kv = tide.PagedKV(pages, hq, hkv, d, bt)
+    kv.append(k[:prefix].cuda(), v[:prefix].cuda(), [0], [prefix])
+    return kv, q.cuda(), k[prefix:].cuda(), v[prefix:].cuda(), ref, lse
+
+
+CASES = {
+    "unmasked_jump": (4, 1, 128, 300, 40, {130: 64.0}),
+    "two_jumps": (8, 2, 64, 500, 70, {70: 40.0, 333: 300.0}),
+    "diagonal_jump": (7, 1, 128, 128, 100, {150: 200.0}),
+    "first_tile_largest": (4, 2, 128, 260, 33, {5: 300.0}),
+    "last_key": (2, 2, 64, 255, 1, {255: 500.0}),
+    "long_split": (4, 2, 128, 2600, 50, {40: 30.0, 1000: 100.0, 2610: 400.0}),
+}
+
+
+@pytest.mark.parametrize("split", ["0", "1"])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_score_jumps(name, split, monkeypatch):
+    monkeypatch.setenv("TIDE_EXTEND_SPLIT", split)
+    hq, hkv, d, p, e, scaled = CASES[name]
+    log("jump case %s split %s" % (name, split))
+    kv, q, kn, vn, ref, ref_lse = build(hq, hkv, d, p, e, scaled, seed=len(name))
+    lse = torch.empty((e, hq), dtype=torch.float32, device="cuda")
+    fused = kv.extend_append(q, kn, vn, [p], [e], lse=lse)
+    assert_close(fused, ref, "%s fused" % name)
+    # an fp32 log-sum-exp of magnitude 1e3 is good to about 1e-4 relative to its size
+    tol = 1e-3 + 1e-6 * float(np.abs(ref_lse).max())
+    assert_lse(lse, ref_lse, "%s fused" % name, tol)
+    assert torch.equal(kv.extend(q, [p], [e]), fused)
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_bad_key_stays_in_its_rows(value):
+    """A key that holds NaN (or infinities, whose scores are infinite or NaN) reaches exactly
+    the rows that see it."""
+    p, e, at = 300, 40, 320
+    log("bad key %s" % value)
+    kv, q, kn, vn, _, _ = build(4, 1, 128, p, e, {}, seed=3, bad=(at, value))
+    good = build(4, 1, 128, p, e, {}, seed=3)
+    out = host_f64(kv.extend_append(q, kn, vn, [p], [e]))
+    ref = host_f64(good[0].extend_append(*good[1:4], [p], [e]))
+    assert np.array_equal(out[: at - p], ref[: at - p])
+    assert np.isnan(out[at - p:]).any(axis=-1).any(axis=-1).all()
