@@ -203,10 +203,10 @@ TIDE_API int tide_extend_append_attn(const void* q, const void* k_new, const voi
  * Decode attention: one query token per task (the action tokens generated between
  * environment turns, Section 2.1) over its whole context of kv_lens[b] >= 1 positions,
  * which include the token itself (append it first).  q/out: bf16 [num_tasks][Hq][d];
- * lse: fp32 [num_tasks][Hq] or NULL.  The context is split into chunks processed in
- * parallel and merged by log-sum-exp weights (split-K).  num_splits == 0 chooses the
- * chunk size automatically; num_splits > 0 caps the number of chunks per task at that
- * value.  Results for different split counts agree to fp32 rounding.
+ * lse: fp32 [num_tasks][Hq] or NULL.  The context is split into parts processed in
+ * parallel and merged by log-sum-exp weights (split-K).  num_splits == 0 leaves the split
+ * to the library; num_splits > 0 cuts every context into chunks, at most that many per
+ * task.  Results for different split counts agree to fp32 rounding.
  * Every K/V page is streamed with the non-temporal cache hint, since each task's context
  * is read once.  Tasks whose block tables share pages (a GRPO group's prompt) should go
  * through tide_decode_attn_shared, which reads a shared prefix once per group; here each

@@ -21,6 +21,7 @@ BUILD_DIR = os.path.join(PKG, "_build")
 LIB_PATH = os.path.join(PKG, "libtide.so")
 
 HIP_SOURCES = ["tide_api.hip", "attn_extend.hip", "attn_extend_append.hip", "attn_decode.hip",
+               "attn_decode_stream.hip",
                "kv_append.hip"]
 CXX_SOURCES = ["plan.cpp", "ctb.cpp"]
 ARCH = "gfx950"

@@ -28,6 +28,11 @@ struct Plan {
   // the split kernel merges (fold_merge: few splits per task) instead of a merge kernel
   size_t tickets_off = 0;
   bool fold_merge = false;
+  // decode with the library's own split (make_plan_decode): StreamItems, one per run
+  bool stream = false;
+  int32_t num_runs = 0;
+  int32_t steps = 0;       // key steps per run
+  int32_t last_steps = 0;  // of the last run
   int64_t row_slots = 0;  // partial row slots (each holds every query head)
   // the planner's run-time estimates (microseconds) of the plain and chosen extend plans;
   // 0 when the call was too large to consider splitting
@@ -56,6 +61,11 @@ int check_dims(const tide_dims* dims);
 int make_plan(int op, int32_t num_tasks, const int32_t* lens_a, const int32_t* lens_b,
               const tide_dims& dims, int32_t num_splits, int32_t bt_stride, bool build_blob,
               Plan* plan);
+
+// Decode: runs of equal length when the library chooses the split (num_splits == 0) and the call's
+// steps can be counted in 32 bits, else the chunk plan of make_plan.
+int make_plan_decode(int32_t num_tasks, const int32_t* kv_lens, const tide_dims& dims,
+                     int32_t num_splits, int32_t bt_stride, bool build_blob, Plan* plan);
 
 // Shared-prefix decode: groups are consecutive task ranges [group_start[g],
 // group_start[g+1]); the first shared_lens[g] keys (a multiple of the page size, below

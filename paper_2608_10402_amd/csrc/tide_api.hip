@@ -261,8 +261,7 @@ int run_decode(const void* q, const void* k_new, const void* v_new, const void* 
   if (num_tasks == 0) return TIDE_OK;
   if (num_pages <= 0 || bt_stride <= 0) return TIDE_ERR_INVALID_ARG;
   Plan plan;
-  rc = make_plan(TIDE_OP_DECODE, num_tasks, kv_lens, nullptr, *dims, num_splits, bt_stride, true,
-                 &plan);
+  rc = make_plan_decode(num_tasks, kv_lens, *dims, num_splits, bt_stride, true, &plan);
   if (rc != TIDE_OK) return rc;
   if (!q || !k_pool || !v_pool || !block_table || !out) return TIDE_ERR_INVALID_ARG;
   if (fused && (!k_new || !v_new)) return TIDE_ERR_INVALID_ARG;
@@ -280,6 +279,34 @@ int run_decode(const void* q, const void* k_new, const void* v_new, const void* 
     if (workspace_bytes < plan.total_bytes) return TIDE_ERR_CAPACITY;
     rc = upload(plan, workspace, s);
     if (rc != TIDE_OK) return rc;
+  }
+  if (plan.stream) {
+    StreamArgs a;
+    a.q = static_cast<const uint16_t*>(q);
+    a.k_pool = static_cast<const uint16_t*>(k_pool);
+    a.v_pool = static_cast<const uint16_t*>(v_pool);
+    a.block_table = block_table;
+    a.num_pages = num_pages;
+    a.bt_stride = bt_stride;
+    a.num_q_heads = dims->num_q_heads;
+    a.num_kv_heads = dims->num_kv_heads;
+    a.group = dims->num_q_heads / dims->num_kv_heads;
+    a.scale_log2 = dims->sm_scale * 1.44269504088896340736f;
+    a.num_runs = plan.num_runs;
+    a.num_tasks = num_tasks;
+    a.steps = plan.steps;
+    a.last_steps = plan.last_steps;
+    a.tasks = at<TaskDesc>(workspace, plan.tasks_off);
+    a.items = at<StreamItem>(workspace, plan.items_off);
+    a.part_o = at_mut<float>(workspace, plan.part_o_off);
+    a.part_ml = at_mut<float>(workspace, plan.part_ml_off);
+    a.tickets = at_mut<int32_t>(workspace, plan.tickets_off);
+    a.out = static_cast<uint16_t*>(out);
+    a.lse = lse;
+    a.error_flags = at_mut<int32_t>(workspace, 0);
+    a.k_new = static_cast<const uint16_t*>(k_new);
+    a.v_new = static_cast<const uint16_t*>(v_new);
+    return finish(launch_decode_stream(a, dims->head_dim, s), workspace, s);
   }
   DecodeArgs a;
   a.q = static_cast<const uint16_t*>(q);
@@ -324,7 +351,9 @@ TIDE_API int tide_workspace_size(int op, int32_t num_tasks, const int32_t* lens_
     int rc = check_dims(dims);
     if (rc != TIDE_OK) return rc;
     Plan plan;
-    rc = make_plan(op, num_tasks, lens_a, lens_b, *dims, num_splits, -1, false, &plan);
+    rc = op == TIDE_OP_DECODE
+             ? make_plan_decode(num_tasks, lens_a, *dims, num_splits, -1, false, &plan)
+             : make_plan(op, num_tasks, lens_a, lens_b, *dims, num_splits, -1, false, &plan);
     if (rc != TIDE_OK) return rc;
     *bytes_out = plan.total_bytes;
     return TIDE_OK;
@@ -341,13 +370,16 @@ TIDE_API int tide_plan_info_get(int op, int32_t num_tasks, const int32_t* lens_a
     int rc = check_dims(dims);
     if (rc != TIDE_OK) return rc;
     Plan plan;
-    rc = make_plan(op, num_tasks, lens_a, lens_b, *dims, num_splits, -1, false, &plan);
+    rc = op == TIDE_OP_DECODE
+             ? make_plan_decode(num_tasks, lens_a, *dims, num_splits, -1, false, &plan)
+             : make_plan(op, num_tasks, lens_a, lens_b, *dims, num_splits, -1, false, &plan);
     if (rc != TIDE_OK) return rc;
     *out = tide_plan_info{};
     out->num_items = plan.num_items;
     out->workspace_bytes = plan.total_bytes;
     if (op == TIDE_OP_DECODE) {
-      out->waves_per_group = decode_waves(plan.num_items);
+      out->waves_per_group =
+          plan.stream ? stream_waves(plan.num_items) : decode_waves(plan.num_items);
       out->max_splits = plan.max_splits;
       out->merge_in_kernel = plan.fold_merge ? 1 : 0;
     } else if (op == TIDE_OP_KV_APPEND) {

@@ -4,6 +4,12 @@
 
 #include <stdint.h>
 
+#ifdef __HIPCC__
+#define TIDE_HD __host__ __device__
+#else
+#define TIDE_HD
+#endif
+
 namespace tide {
 
 constexpr int kPage = 16;         // tokens per page
@@ -69,6 +75,73 @@ struct DecodeItem {
   int32_t split;
   int32_t k_begin;
 };
+
+// Decode work of one run when the split count is left to the library: the tasks' 32-key
+// steps, laid end to end, are cut into equal runs, and one wave per kv head takes the run
+// that starts at `step` of `task` and may cross into the next tasks.
+struct StreamItem {
+  int32_t task;
+  int32_t step;
+  int32_t kv_len;  // of `task`, so that a wave's first loads wait for one record only
+  int32_t pad;
+};
+
+// A task cut by the ends of runs: run w0 + i holds part i of n (of every kv head).
+struct StreamUnit {
+  int32_t w0, n;
+  bool ends_inside;  // the last part ends before its run does
+};
+
+// The cut task that run w has steps begin .. begin + part - 1 of, in runs of `run` steps.
+TIDE_HD inline StreamUnit stream_unit(int32_t w, int32_t begin, int32_t part, int32_t steps,
+                                      int32_t run) {
+  StreamUnit u;
+  const int32_t i = begin / run + (begin % run ? 1 : 0);        // this run's part
+  const int32_t first = i == 0 ? part : begin - (i - 1) * run;  // steps of part 0
+  const int32_t rest = steps - first;
+  u.w0 = w - i;
+  u.n = 1 + rest / run + (rest % run ? 1 : 0);
+  u.ends_inside = rest % run != 0;
+  return u;
+}
+
+// Waves per workgroup of a call of `items` waves (runs x kv heads), each workgroup taking that
+// many consecutive runs of one kv head: 8 combine more partials in LDS; a call of up to 256
+// waves takes 4, so that it spreads over more CUs.
+TIDE_HD inline int32_t stream_waves(int64_t items) { return items > 256 ? 8 : 4; }
+
+// Where the partials of one kv head's cut tasks go.  The parts that reach their run's end are
+// combined per workgroup, into one slot for each (workgroup, task); a part that ends inside
+// its run has a slot of its own, at most one for a task and one for a run.  Along the runs
+// either the workgroup or the task grows from one such part to the next, so their sum is a
+// slot index; where tasks outnumber runs, the (first) run is a smaller one.
+struct StreamSlots {
+  int32_t runs, tasks, per;  // per: runs of a workgroup
+  TIDE_HD int32_t groups() const { return (runs + per - 1) / per; }
+  TIDE_HD int32_t open_slots() const {
+    return (int64_t)groups() + tasks < runs ? groups() + tasks : runs;
+  }
+  TIDE_HD int32_t count() const { return open_slots() + (tasks < runs ? tasks : runs); }
+  TIDE_HD int32_t open(int32_t run, int32_t task) const {
+    return (int64_t)groups() + tasks < runs ? run / per + task : run;
+  }
+  TIDE_HD int32_t ended(int32_t run, int32_t task) const {
+    return open_slots() + (tasks < runs ? task : run);
+  }
+};
+
+// The number of a cut task's partials, and the slot of the e-th in key order.
+TIDE_HD inline int32_t stream_parts(const StreamUnit& u, int32_t per) {
+  const int32_t wf = u.w0 + u.n - (u.ends_inside ? 2 : 1);
+  return wf / per - u.w0 / per + 1 + (u.ends_inside ? 1 : 0);
+}
+
+TIDE_HD inline int32_t stream_slot(const StreamUnit& u, const StreamSlots& s, int32_t task,
+                                   int32_t e) {
+  if (u.ends_inside && e == stream_parts(u, s.per) - 1) return s.ended(u.w0 + u.n - 1, task);
+  const int32_t w = (u.w0 / s.per + e) * s.per;
+  return s.open(w > u.w0 ? w : u.w0, task);
+}
 
 // Shared-prefix decode item: keys [k_begin, k_end) for tasks first_task ..
 // first_task + ntasks - 1 and one kv head.  With ntasks > 1 the keys lie in the prefix
@@ -178,6 +251,36 @@ struct DecodeArgs {
   // the work list); the split that brings it to the task's split count merges that kv
   // head's rows.  Null for the shared-prefix variant, which merges in a second kernel.
   int32_t* tickets;
+};
+
+struct StreamArgs {
+  const uint16_t* q;
+  const uint16_t* k_pool;
+  const uint16_t* v_pool;
+  const int32_t* block_table;
+  int64_t num_pages;
+  int32_t bt_stride;
+  int32_t num_q_heads;
+  int32_t num_kv_heads;
+  int32_t group;
+  float scale_log2;
+  int32_t num_runs;
+  int32_t steps;       // steps per run
+  int32_t last_steps;  // steps of the last run, 1 .. steps
+  const TaskDesc* tasks;  // prefix + extend == kv_len
+  const StreamItem* items;
+  int32_t num_tasks;
+  // partials: per kv head the slots of StreamSlots
+  float* part_o;     // [Hkv][slots][group][d] unnormalised outputs
+  float* part_ml;    // [Hkv][slots][group][4]: max (base-2 units), sum of the bf16-rounded
+                     // weights, exact fp32 sum, unused
+  int32_t* tickets;  // [Hkv][num_runs] arrivals of the task whose first part run w holds, zero
+                     // at launch
+  uint16_t* out;
+  float* lse;
+  int32_t* error_flags;
+  const uint16_t* k_new;  // fused append as in DecodeArgs
+  const uint16_t* v_new;
 };
 
 }  // namespace tide
