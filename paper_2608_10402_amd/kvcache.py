@@ -51,46 +51,69 @@ class PagedKV:
             self._ws = _lib.alloc_workspace(max(nbytes, 1 << 16), self.device)
         return self._ws
 
+    def _call(self, size, call):
+        """call(workspace), with a workspace that is large enough.  The library plans every
+        call and refuses a workspace too small for it before any device work, so a call is
+        planned once as a rule, and its size asked for only then."""
+        if self._ws is None:
+            self.workspace(size())
+        try:
+            call(self._ws)
+        except _lib.TideError as e:
+            if e.status != _lib.TIDE_ERR_CAPACITY:
+                raise
+            need = size()
+            if need <= self._ws.numel():  # the block table's capacity, not the workspace's
+                raise
+            call(self.workspace(need))
+
     def append(self, k_new, v_new, prefix_lens, extend_lens, stream=None):
-        ws = self.workspace(_lib.tide_workspace_size(_lib.TIDE_OP_KV_APPEND, prefix_lens,
-                                                     extend_lens, self.dims))
-        _lib.tide_kv_append(k_new, v_new, self.k_pool, self.v_pool, self.block_table,
-                            prefix_lens, extend_lens, self.dims, ws, stream)
+        self._call(lambda: _lib.tide_workspace_size(_lib.TIDE_OP_KV_APPEND, prefix_lens,
+                                                    extend_lens, self.dims),
+                   lambda ws: _lib.tide_kv_append(k_new, v_new, self.k_pool, self.v_pool,
+                                                  self.block_table, prefix_lens, extend_lens,
+                                                  self.dims, ws, stream))
 
     def extend(self, q, prefix_lens, extend_lens, out=None, lse=None, stream=None):
         out = torch.empty_like(q) if out is None else out
-        ws = self.workspace(_lib.tide_workspace_size(_lib.TIDE_OP_EXTEND, prefix_lens,
-                                                     extend_lens, self.dims))
-        _lib.tide_extend_attn(q, self.k_pool, self.v_pool, self.block_table, prefix_lens,
-                              extend_lens, self.dims, out, lse, ws, stream)
+        self._call(lambda: _lib.tide_workspace_size(_lib.TIDE_OP_EXTEND, prefix_lens, extend_lens,
+                                                    self.dims),
+                   lambda ws: _lib.tide_extend_attn(q, self.k_pool, self.v_pool, self.block_table,
+                                                    prefix_lens, extend_lens, self.dims, out, lse,
+                                                    ws, stream))
         return out
 
     def extend_append(self, q, k_new, v_new, prefix_lens, extend_lens, out=None, lse=None,
                       stream=None):
         """Append the new tokens' K/V and run extend attention, fused in one call."""
         out = torch.empty_like(q) if out is None else out
-        ws = self.workspace(_lib.tide_workspace_size(_lib.TIDE_OP_EXTEND, prefix_lens,
-                                                     extend_lens, self.dims))
-        _lib.tide_extend_append_attn(q, k_new, v_new, self.k_pool, self.v_pool, self.block_table,
-                                     prefix_lens, extend_lens, self.dims, out, lse, ws, stream)
+        self._call(lambda: _lib.tide_workspace_size(_lib.TIDE_OP_EXTEND, prefix_lens, extend_lens,
+                                                    self.dims),
+                   lambda ws: _lib.tide_extend_append_attn(q, k_new, v_new, self.k_pool,
+                                                           self.v_pool, self.block_table,
+                                                           prefix_lens, extend_lens, self.dims,
+                                                           out, lse, ws, stream))
         return out
 
     def decode(self, q, kv_lens, num_splits: int = 0, out=None, lse=None, stream=None):
         out = torch.empty_like(q) if out is None else out
-        ws = self.workspace(_lib.tide_workspace_size(_lib.TIDE_OP_DECODE, kv_lens, None,
-                                                     self.dims, num_splits))
-        _lib.tide_decode_attn(q, self.k_pool, self.v_pool, self.block_table, kv_lens, self.dims,
-                              out, lse, num_splits, ws, stream)
+        self._call(lambda: _lib.tide_workspace_size(_lib.TIDE_OP_DECODE, kv_lens, None, self.dims,
+                                                    num_splits),
+                   lambda ws: _lib.tide_decode_attn(q, self.k_pool, self.v_pool, self.block_table,
+                                                    kv_lens, self.dims, out, lse, num_splits, ws,
+                                                    stream))
         return out
 
     def decode_append(self, q, k_new, v_new, kv_lens, num_splits: int = 0, out=None, lse=None,
                       stream=None):
         """Append each task's newest token (position kv_lens - 1) and decode, fused."""
         out = torch.empty_like(q) if out is None else out
-        ws = self.workspace(_lib.tide_workspace_size(_lib.TIDE_OP_DECODE, kv_lens, None,
-                                                     self.dims, num_splits))
-        _lib.tide_decode_append_attn(q, k_new, v_new, self.k_pool, self.v_pool, self.block_table,
-                                     kv_lens, self.dims, out, lse, num_splits, ws, stream)
+        self._call(lambda: _lib.tide_workspace_size(_lib.TIDE_OP_DECODE, kv_lens, None, self.dims,
+                                                    num_splits),
+                   lambda ws: _lib.tide_decode_append_attn(q, k_new, v_new, self.k_pool,
+                                                           self.v_pool, self.block_table, kv_lens,
+                                                           self.dims, out, lse, num_splits, ws,
+                                                           stream))
         return out
 
     def decode_noalloc(self, q, kv_lens, num_splits: int = 0, out=None, lse=None, stream=None):
@@ -103,17 +126,19 @@ class PagedKV:
     def decode_shared(self, q, kv_lens, group_start, shared_lens, num_splits: int = 0, out=None,
                       lse=None, stream=None):
         out = torch.empty_like(q) if out is None else out
-        ws = self.workspace(_lib.tide_workspace_size_shared(kv_lens, group_start, shared_lens,
-                                                            self.dims, num_splits))
-        _lib.tide_decode_attn_shared(q, self.k_pool, self.v_pool, self.block_table, kv_lens,
-                                     group_start, shared_lens, self.dims, out, lse, num_splits,
-                                     ws, stream)
+        self._call(lambda: _lib.tide_workspace_size_shared(kv_lens, group_start, shared_lens,
+                                                           self.dims, num_splits),
+                   lambda ws: _lib.tide_decode_attn_shared(q, self.k_pool, self.v_pool,
+                                                           self.block_table, kv_lens, group_start,
+                                                           shared_lens, self.dims, out, lse,
+                                                           num_splits, ws, stream))
         return out
 
     def prefill(self, q, seq_lens, out=None, lse=None, stream=None):
         out = torch.empty_like(q) if out is None else out
-        ws = self.workspace(_lib.tide_workspace_size(_lib.TIDE_OP_FULL_PREFILL, seq_lens, None,
-                                                     self.dims))
-        _lib.tide_full_prefill_attn(q, self.k_pool, self.v_pool, self.block_table, seq_lens,
-                                    self.dims, out, lse, ws, stream)
+        self._call(lambda: _lib.tide_workspace_size(_lib.TIDE_OP_FULL_PREFILL, seq_lens, None,
+                                                    self.dims),
+                   lambda ws: _lib.tide_full_prefill_attn(q, self.k_pool, self.v_pool,
+                                                          self.block_table, seq_lens, self.dims,
+                                                          out, lse, ws, stream))
         return out
