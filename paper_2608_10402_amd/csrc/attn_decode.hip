@@ -455,12 +455,12 @@ void decode_split_kernel(DecodeArgs a) {
   }
 }
 
-// One wave per (task, query head): combine the task's split partials.  kSkipSingle: a
-// task with one split already wrote its rows (plain decode).
+// kMergeRows (task, query head) pairs per wave: combine the task's split partials.
+// kSkipSingle: a task with one split already wrote its rows (plain decode).
 template <int D, bool kSkipSingle>
 __global__ __launch_bounds__(kMergeWaves * 64) void decode_merge_kernel(DecodeArgs a) {
-  // wave-uniform and 32-bit (the launch has num_tasks * Hq < 2^31 waves)
-  const int row = (int)blockIdx.x * kMergeWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // 32-bit (the launch has num_tasks * Hq < 2^31 rows)
+  const int row = (int)(blockIdx.x * (kMergeWaves * kMergeRows<D>) + threadIdx.x / (D / 4));
   if (row >= a.num_tasks * a.num_q_heads) return;
   const int task = row / a.num_q_heads;
   const int n = a.tasks[task].aux;
@@ -487,9 +487,10 @@ hipError_t launch(const DecodeArgs& a, hipStream_t stream) {
   }
   if (!kShared && a.tickets) return hipSuccess;  // merged inside the split kernel
   const int64_t rows = (int64_t)a.num_tasks * a.num_q_heads;
-  if (rows >= INT32_MAX - kMergeWaves) return hipErrorInvalidValue;
+  constexpr int kRows = kMergeWaves * kMergeRows<D>;
+  if (rows >= INT32_MAX - kRows) return hipErrorInvalidValue;
   if (rows > 0) {
-    const int blocks = (int)((rows + kMergeWaves - 1) / kMergeWaves);
+    const int blocks = (int)((rows + kRows - 1) / kRows);
     hipLaunchKernelGGL((decode_merge_kernel<D, !kShared>), dim3(blocks), dim3(kMergeWaves * 64),
                        0, stream, a);
   }

@@ -7,18 +7,17 @@ namespace kern {
 
 constexpr int kMergeWaves = 4;
 
-// One wave per (packed row, query head) of a split-KV call: combines the row's chunk
-// partials; rows that were not split were written by the attention kernel.
+// kMergeRows (packed row, query head) pairs of a split-KV call per wave: combines each row's
+// chunk partials; rows that were not split were written by the attention kernel.
 template <int D>
 __global__ __launch_bounds__(kMergeWaves * 64) void extend_merge_kernel(ExtendArgs a) {
-  // wave-uniform and 32-bit (the launch has total_rows * Hq < 2^31 waves)
-  const int wi = (int)blockIdx.x * kMergeWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // 32-bit (the launch has total_rows * Hq < 2^31 rows)
+  const int wi = (int)(blockIdx.x * (kMergeWaves * kMergeRows<D>) + threadIdx.x / (D / 4));
   if (wi >= a.total_rows * a.num_q_heads) return;
   const int row = wi / a.num_q_heads;
   const int head = wi - row * a.num_q_heads;
   const int64_t w = wi;
   const MergeRow mr = a.merge_rows[row];
-  if (mr.nsplit == 0) return;
   const int64_t s0 = (int64_t)mr.base * a.num_q_heads + head;
   const int64_t ss = (int64_t)mr.stride * a.num_q_heads;
   merge_partials<D>(a.part_ml + s0 * 4, ss * 4, a.part_o + s0 * D, ss * D, mr.nsplit,
@@ -44,9 +43,10 @@ hipError_t launch(const ExtendArgs& a, hipStream_t stream) {
   else
     e = a.chunk_items ? launch_attn<D, true>(a, stream) : launch_attn<D, false>(a, stream);
   if (e != hipSuccess || !a.chunk_items || !a.merge_rows) return e;
-  const int64_t waves = (int64_t)a.total_rows * a.num_q_heads;
-  if (waves >= INT32_MAX - kMergeWaves) return hipErrorInvalidValue;
-  const int blocks = (int)((waves + kMergeWaves - 1) / kMergeWaves);
+  const int64_t rows = (int64_t)a.total_rows * a.num_q_heads;
+  constexpr int kRows = kMergeWaves * kMergeRows<D>;
+  if (rows >= INT32_MAX - kRows) return hipErrorInvalidValue;
+  const int blocks = (int)((rows + kRows - 1) / kRows);
   hipLaunchKernelGGL((extend_merge_kernel<D>), dim3(blocks), dim3(kMergeWaves * 64), 0, stream, a);
   return hipGetLastError();
 }
