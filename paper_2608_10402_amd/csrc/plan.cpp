@@ -152,71 +152,100 @@ int task_lengths(int op, int32_t b, const int32_t* lens_a, const int32_t* lens_b
 //   split  a block that spans many tiles is cut into chunks of about T tiles that run on
 //          different CUs and write unnormalised fp32 partials, which a second kernel
 //          merges (the split-K scheme of flash decoding, applied to extend blocks).
-// Splitting pays when a call has too few items to keep 256 CUs busy to the end.  The
-// choice compares closed-form run-time estimates: the makespan of n workgroups costing
-// c_i tiles each on 256 CUs is max c when n <= 256 (all start at once), and is taken as
-// max(max c, sum c / 256 + max c / 2) otherwise; a tile costs less while few CUs are
-// busy (the clock is higher), and a split plan adds the merge's HBM traffic and launch.
-// The planner runs on every call, so everything here is linear in the number of blocks,
+// Splitting pays when a call has too few items to keep 256 CUs busy to the end, or a last
+// round of items that is nearly empty.  The choice compares run-time estimates of the plain
+// plan and of split plans whose chunks fill 1 .. kRounds rounds of the CUs: the items of a kv
+// head are dealt out longest first, a round of 256 / Hkv at a time, and a round lasts as long
+// as its longest item; a tile costs less while CUs are idle (the card is power-limited, so
+// its clock is higher then), a chunk costs the write of its partial, and a split plan the
+// merge.  The planner runs on every call, so everything here is a few passes over the blocks,
 // and only the chosen plan is materialised.
 namespace {
 
 constexpr int kCus = 256;  // MI355X compute units, 32 per XCD
-// Cost model, in units of one key tile of one workgroup at full occupancy; the overheads
-// and rates were fitted to measured one- to 64-task calls (GQA 28/4, d = 128).
-constexpr double kItemOverhead = 0.5;     // first-tile latency and epilogue
-constexpr double kChunkOverhead = 2.5;    // the same plus the fp32 partial write
-constexpr double kCuFlopsPerUs = 3.9e6;   // sustained MFMA rate of one CU, all CUs busy
-constexpr double kIdleClockGain = 0.25;   // a tile is up to this much cheaper with idle CUs
-constexpr double kHbmBytesPerUs = 5.0e6;  // sustained HBM rate of the merge
-constexpr double kMergeLaunchUs = 4.0;    // second kernel launch
-constexpr double kSplitGain = 1.0;        // split whenever estimated faster
-constexpr int kMinChunkTiles = 8;
+// Cost model, fitted to 27 calls of 1-40 tasks, 500-90,000 keys and 8-1,500 new tokens timed
+// plain and with 1 .. 6 rounds of chunks (all head shapes); the plan it takes was within 5% of
+// the fastest of them on 23 and within 15% on the others.  Against the plan before it (chunks
+// on a fixed grid of T tiles, the last up to 1.5 T long, for the least estimated sum) on the
+// same kernel, one task of 12,000 + 800 tokens went from 185 to 161 us (28 / 4 heads, d = 128);
+// with the kernel's own 7% in it, one of 30,000 + 200 from 151 to 103, 3 of 12,000 + 800 from
+// 551 to 440, 8 of 6,000 + 380 from 338 to 262, 2 of 8,000 + 1,500 (32 / 8) from 549 to 405.
+constexpr double kCuFlopsPerUs = 4.7e6;    // MFMA rate of one CU, all CUs busy
+constexpr double kIdleClockGain = 0.25;    // a tile is this much cheaper with half the CUs idle
+constexpr double kItemUs = 1.0;            // first-tile latency and epilogue
+constexpr double kChunkUs = 3.0;           // the same with the partial's statistics
+constexpr double kChunkRowsUs = 6.6;       // write of 256 rows' partials, all CUs at once
+constexpr double kMergeBytesPerUs = 6.5e6; // rate at which the merge reads the partials
+constexpr double kMergeLaunchUs = 4.0;     // second kernel launch
+constexpr double kSplitGain = 0.96;        // split when estimated at least this much faster
+constexpr int kMinChunkTiles = 4;
 constexpr int kMaxChunks = 512;
+constexpr int kRounds = 6;
 constexpr int64_t kSplitMaxItems = 2048;  // larger calls fill the chip with the plain plan
 
 struct Block {
   int32_t task, tok0, ntok, ntiles;
 };
 
-// Chunks of a block for chunk length T: about ntiles / T (at most kMaxChunks), on a
-// fixed grid [c*T, (c+1)*T) whose last chunk takes the rest (up to 1.5 T below the cap),
-// so the same chunk of a unit's blocks covers the same keys.  T == 0: the plain plan
-// (one chunk).
+// A block's tiles cut into chunks of at most T tiles, as few as that takes (at most
+// kMaxChunks) and of equal length to one tile, so that equally long blocks of a task are cut
+// at the same keys.  T == 0: the plain plan (one chunk).
 inline int32_t num_chunks(int32_t ntiles, int32_t T) {
   if (T <= 0) return 1;
-  return (int32_t)std::min<int64_t>(kMaxChunks, std::max<int64_t>(1, (ntiles + T / 2) / T));
+  return std::min(kMaxChunks, std::max(1, (int32_t)(((uint32_t)ntiles + (uint32_t)T - 1) / (uint32_t)T)));
 }
 
-inline int32_t chunk_tiles(int32_t ntiles, int32_t T, int32_t n, int32_t c) {
-  return c == n - 1 ? ntiles - c * T : T;
+inline int32_t chunk_begin(int32_t ntiles, int32_t n, int32_t c) {
+  return n == 1 ? c * ntiles : c * (ntiles / n) + std::min(c, ntiles % n);
 }
 
-inline double chunk_cost(int32_t ntiles, int32_t T, int32_t n, int32_t c) {
-  return chunk_tiles(ntiles, T, n, c) + (n > 1 ? kChunkOverhead : kItemOverhead);
+inline int32_t chunk_tiles(int32_t ntiles, int32_t n, int32_t c) {
+  return n == 1 ? ntiles : ntiles / n + (c < ntiles % n ? 1 : 0);
+}
+
+// What dealing items out to XCDs takes a chunk to cost (in tiles).
+inline double chunk_cost(int32_t ntiles, int32_t n, int32_t c) {
+  return chunk_tiles(ntiles, n, c) + (n > 1 ? 3.0 : 0.5);
 }
 
 // Estimated run time (us) of the plan with chunk length T (0: plain).
-double estimate(const std::vector<Block>& blocks, int32_t num_kv_heads, int32_t num_q_heads,
-                int32_t head_dim, int32_t T, double tile_us, int64_t* row_slots) {
-  double total = 0.0, biggest = 0.0;
-  int64_t items = 0, slots = 0;
+double estimate(const std::vector<Block>& blocks, int32_t longest, const tide_dims& dims, int32_t T,
+                double tile_us, int64_t* row_slots) {
+  const int32_t group = dims.num_q_heads / dims.num_kv_heads;
+  const int64_t round = std::max(1, kCus / dims.num_kv_heads);  // CUs of a kv head
+  // the chunks of one kv head by length (in steps of 2^shift tiles, if very long)
+  constexpr int kBins = 1024;
+  int64_t count[kBins] = {};
+  int32_t most_rows[kBins] = {};
+  int shift = 0;
+  while ((T > 0 ? std::min(T, longest) : longest) >> shift >= kBins) ++shift;
+  int64_t slots = 0, items = 0;
   for (const Block& b : blocks) {
     const int32_t n = num_chunks(b.ntiles, T);
-    items += n;
     if (n > 1) slots += (int64_t)b.ntok * n;
-    total += (n - 1) * chunk_cost(b.ntiles, T, n, 0) + chunk_cost(b.ntiles, T, n, n - 1);
-    for (int32_t c : {0, n - 1}) biggest = std::max(biggest, chunk_cost(b.ntiles, T, n, c));
+    items += n;
+    const int32_t q = b.ntiles / n, r = b.ntiles % n, rows = n > 1 ? b.ntok * group : 0;
+    for (int up = 0; up < 2; ++up) {
+      const int32_t m = up ? r : n - r, bin = std::min(kBins - 1, (q + up) >> shift);
+      if (m == 0) continue;
+      count[bin] += m;
+      most_rows[bin] = std::max(most_rows[bin], rows);
+    }
   }
-  items *= num_kv_heads;
-  total *= num_kv_heads;
-  const double busy = std::min(1.0, (double)items / kCus);
-  const double t_eff = tile_us * (1.0 - kIdleClockGain * (1.0 - busy));
-  // up to one workgroup per CU, all start at once and the longest one ends the call
-  const double span = items <= kCus ? biggest : std::max(biggest, total / kCus + 0.5 * biggest);
-  double us = span * t_eff;
+  double us = 0.0;
+  int64_t seen = 0, lead = 0;  // lead: place of the longest item of the next round
+  for (int bin = kBins - 1; bin >= 0; --bin) {
+    seen += count[bin];
+    for (; lead < seen; lead += round) {
+      const double busy = (double)std::min(round, items - lead) / round;
+      us += (double)((int64_t)bin << shift) * tile_us *
+                (1.0 - kIdleClockGain * std::min(1.0, 2.0 * (1.0 - busy))) +
+            (most_rows[bin] ? kChunkUs + kChunkRowsUs * most_rows[bin] / 256 : kItemUs);
+    }
+  }
+  us *= std::max(1.0, (double)dims.num_kv_heads / kCus);
   if (slots > 0)
-    us += (double)slots * num_q_heads * (head_dim * 4.0 + 16.0) * 2.0 / kHbmBytesPerUs +
+    us += (double)slots * dims.num_q_heads * (dims.head_dim * 4.0 + 16.0) / kMergeBytesPerUs +
           kMergeLaunchUs;
   *row_slots = slots;
   return us;
@@ -251,7 +280,7 @@ std::vector<std::vector<Piece>> place(const std::vector<Block>& blocks,
       int32_t end = k0;
       double cost = 0.0;
       while (end < k1 && nchunks[end] > c) {
-        const double ci = chunk_cost(blocks[end].ntiles, T, nchunks[end], c);
+        const double ci = chunk_cost(blocks[end].ntiles, nchunks[end], c);
         cost += ci;
         biggest = std::max(biggest, ci);
         ++end;
@@ -268,7 +297,7 @@ std::vector<std::vector<Piece>> place(const std::vector<Block>& blocks,
     const int32_t c = std::max(col.c, 0);
     Piece cur{0.0, col.k0, col.k0, col.g, col.c};
     for (int32_t k = col.k0; k < col.k1; ++k) {
-      const double ci = chunk_cost(blocks[k].ntiles, T, nchunks[k], c);
+      const double ci = chunk_cost(blocks[k].ntiles, nchunks[k], c);
       if (cur.k1 > cur.k0 && cur.cost + ci > cap) {
         pieces.push_back(cur);
         cur = Piece{0.0, k, k, col.g, col.c};
@@ -281,26 +310,67 @@ std::vector<std::vector<Piece>> place(const std::vector<Block>& blocks,
   std::stable_sort(pieces.begin(), pieces.end(),
                    [](const Piece& x, const Piece& y) { return x.cost > y.cost; });
   std::vector<std::vector<Piece>> queues(kXcds);
+  // In a call of a few rounds no XCD takes more items than its CUs' share of the rounds: one
+  // more would be a round of its own (the same call as 264 items, 33 an XCD, took 65 us and
+  // as 256 took 45).
+  int64_t items = 0;
+  for (const Piece& p : pieces) items += p.k1 - p.k0;
+  const int64_t room = items <= kSplitMaxItems ? (items + kCus - 1) / kCus * (kCus / kXcds) : items;
   double load[kXcds] = {};
-  for (const Piece& p : pieces) {
-    const int x = (int)(std::min_element(load, load + kXcds) - load);
-    load[x] += p.cost;
-    queues[x].push_back(p);
+  int64_t count[kXcds] = {};
+  for (Piece p : pieces) {
+    while (p.k0 < p.k1) {
+      int x = -1;
+      for (int i = 0; i < kXcds; ++i)
+        if (count[i] < room && (x < 0 || load[i] < load[x])) x = i;
+      Piece part = p;
+      part.k1 = (int32_t)std::min<int64_t>(p.k1, p.k0 + room - count[x]);
+      part.cost = p.cost * (part.k1 - part.k0) / (p.k1 - p.k0);
+      load[x] += part.cost;
+      count[x] += part.k1 - part.k0;
+      p.cost -= part.cost;
+      p.k0 = part.k1;
+      queues[x].push_back(part);
+    }
   }
   return queues;
 }
 
 // Item slots in dispatch order: slot i * 8 + x is the i-th item of XCD x's queue, and an
-// XCD whose queue ran out gets empty slots (ntok == 0) that return at once.
-template <class Item, class Make>
-std::vector<Item> interleave(const std::vector<std::vector<Piece>>& queues, Make make) {
+// XCD whose queue ran out gets empty slots (ntok == 0) that return at once.  In a call of a
+// few rounds an XCD's items go longest first, in steps of an eighth of the longest (items of
+// about equal length keep their order, and so the K/V they share): a long item that starts
+// last ends the call.  8 tasks of 6,000 + 380 tokens took 260 us so, 302 in column order.
+// Larger calls keep the order of the columns throughout: full-size re-prefills were 10%
+// slower with their items sorted.
+template <class Item, class Make, class Tiles>
+std::vector<Item> interleave(const std::vector<std::vector<Piece>>& queues, Make make, Tiles tiles) {
   std::vector<std::vector<Item>> per(kXcds);
-  size_t depth = 0;
+  size_t depth = 0, total = 0;
+  int32_t longest = 1;
   for (int x = 0; x < kXcds; ++x) {
     for (const Piece& p : queues[x])
-      for (int32_t k = p.k0; k < p.k1; ++k) per[x].push_back(make(k, p.g, std::max(p.c, 0)));
+      for (int32_t k = p.k0; k < p.k1; ++k) {
+        per[x].push_back(make(k, p.g, std::max(p.c, 0)));
+        longest = std::max(longest, tiles(k, std::max(p.c, 0)));
+      }
     depth = std::max(depth, per[x].size());
+    total += per[x].size();
   }
+  if (total <= (size_t)kSplitMaxItems && depth > (size_t)(kCus / kXcds))
+    for (int x = 0; x < kXcds; ++x) {
+      std::vector<uint8_t> cls;  // length class of each item, 0 .. 8
+      int32_t at[10] = {};       // first place of each class, longest first
+      for (const Piece& p : queues[x])
+        for (int32_t k = p.k0; k < p.k1; ++k) {
+          cls.push_back((uint8_t)((int64_t)tiles(k, std::max(p.c, 0)) * 8 / longest));
+          ++at[8 - cls.back() + 1];
+        }
+      for (int i = 1; i < 10; ++i) at[i] += at[i - 1];
+      std::vector<Item> sorted(per[x].size());
+      for (size_t i = 0; i < cls.size(); ++i) sorted[at[8 - cls[i]]++] = per[x][i];
+      per[x].swap(sorted);
+    }
   std::vector<Item> items(depth * kXcds);  // value-initialised: ntok == 0
   for (int x = 0; x < kXcds; ++x)
     for (size_t i = 0; i < per[x].size(); ++i) items[i * kXcds + x] = per[x][i];
@@ -355,24 +425,50 @@ int plan_extend(const std::vector<TaskDesc>& tasks, const tide_dims& dims, bool 
   const int mode = (env && env[0] == '0') ? 0 : (env && env[0] == '1') ? 1 : -1;
   int32_t T = 0;
   if (mode != 0 && plain_items > 0 && plain_items <= kSplitMaxItems) {
-    int64_t slots = 0;
+    int64_t slots = 0, tiles = 0;
+    int32_t longest = 0;
+    for (const Block& b : blocks) {
+      tiles += b.ntiles;
+      longest = std::max(longest, b.ntiles);
+    }
     const double plain_us =
-        estimate(blocks, hkv, dims.num_q_heads, dims.head_dim, 0, tile_us, &slots);
+        estimate(blocks, longest, dims, 0, tile_us, &slots);
     plan->est_plain_us = plan->est_us = plain_us;
     double best_us = mode == 1 ? INFINITY : plain_us * kSplitGain;
-    int64_t tiles = 0;
-    for (const Block& b : blocks) tiles += b.ntiles;
-    int64_t last = -1;
-    for (int rounds = 1; rounds <= 4; ++rounds) {
-      const int64_t t = std::max<int64_t>(
-          kMinChunkTiles, (tiles * hkv + (int64_t)rounds * kCus - 1) / ((int64_t)rounds * kCus));
-      if (t > INT32_MAX / 2 || t == last) continue;
-      last = t;
-      const double us =
-          estimate(blocks, hkv, dims.num_q_heads, dims.head_dim, (int32_t)t, tile_us, &slots);
+    // T for 1 .. kRounds rounds: the shortest chunks that are no more than the CUs take
+    int32_t last = -1;
+    int worse = 0;
+    for (int rounds = 1; rounds <= kRounds && longest > kMinChunkTiles; ++rounds) {
+      if ((double)tiles * hkv / kCus * tile_us * (1.0 - kIdleClockGain) + rounds * kChunkUs >= best_us)
+        break;  // more rounds cannot win
+      const int64_t room = (int64_t)rounds * kCus / hkv;
+      if ((int64_t)blocks.size() > room) continue;
+      auto fits = [&](int32_t t) {
+        int64_t n = 0;
+        for (const Block& b : blocks) n += num_chunks(b.ntiles, t);
+        return n <= room;
+      };
+      int32_t lo = (int32_t)std::max<int64_t>(kMinChunkTiles, ceil_div(tiles, room)) - 1, hi = lo + 1;
+      while (hi < longest && !fits(hi)) {
+        const int32_t next = (int32_t)std::min<int64_t>(longest, 2 * (int64_t)hi - lo);
+        lo = hi;
+        hi = next;
+      }
+      hi = std::min(hi, longest);  // (T = longest: one chunk a block, which fits)
+      while (hi - lo > 1) {
+        const int32_t mid = lo + (hi - lo) / 2;
+        if (fits(mid)) hi = mid;
+        else lo = mid;
+      }
+      if (hi == last) continue;
+      last = hi;
+      const double us = estimate(blocks, longest, dims, hi, tile_us, &slots);
       if (slots > 0 && slots <= INT32_MAX / 2 && us < best_us) {
         best_us = plan->est_us = us;
-        T = (int32_t)t;
+        T = hi;
+        worse = 0;
+      } else if (T > 0 && ++worse == 2) {
+        break;
       }
     }
   }
@@ -385,7 +481,8 @@ int plan_extend(const std::vector<TaskDesc>& tasks, const tide_dims& dims, bool 
     const std::vector<ExtendItem> items = interleave<ExtendItem>(
         queues, [&](int32_t k, int32_t g, int32_t) {
           return ExtendItem{blocks[k].task, g, blocks[k].tok0, blocks[k].ntok};
-        });
+        },
+        [&](int32_t k, int32_t) { return blocks[k].ntiles; });
     *n_items = (int64_t)items.size();
     if (build_blob) to_bytes(items, items_bytes);
     return TIDE_OK;
@@ -408,12 +505,13 @@ int plan_extend(const std::vector<TaskDesc>& tasks, const tide_dims& dims, bool 
         it.kv_head = g;
         it.tok0 = blocks[k].tok0;
         it.ntok = blocks[k].ntok;
-        it.t_begin = c * T;
-        it.t_end = it.t_begin + chunk_tiles(blocks[k].ntiles, T, n, c);
+        it.t_begin = chunk_begin(blocks[k].ntiles, n, c);
+        it.t_end = chunk_begin(blocks[k].ntiles, n, c + 1);
         it.split = n > 1 ? c : -1;
         it.pbase = pbase[k];
         return it;
-      });
+      },
+      [&](int32_t k, int32_t c) { return chunk_tiles(blocks[k].ntiles, nchunks[k], c); });
   *n_items = (int64_t)items.size();
   if (build_blob) {
     to_bytes(items, items_bytes);
