@@ -71,8 +71,9 @@
  * No C++ exception or abort crosses this interface.  The library never allocates
  * device memory at run time (its one static device array, the scratch of
  * tide_decode_attn_noalloc, comes with the code object); it keeps a small pinned,
- * device-mapped host staging ring (created lazily, released by tide_shutdown) from which
- * a copy kernel on `stream` moves each call's work list into the workspace.  Calls that
+ * device-mapped host staging ring (created lazily, released by tide_shutdown) in which a
+ * small call's kernel reads its work list, and from which a copy kernel on `stream` moves
+ * a larger one's into the workspace.  Calls that
  * take a workspace are thread-safe when each call in flight has its own workspace.
  */
 #ifndef TIDE_H_

@@ -401,6 +401,7 @@ void decode_stream_kernel(StreamArgs a) {
   }
   if (lane == 0) open_task[wave] = has_final ? cu.task : -1;
   __syncthreads();
+  if (a.reads.done && threadIdx.x == 0) plan_read(a.reads, blockIdx.x);
 
   // Merges every part of a task in key order and writes this head's rows.
   auto merge = [&](auto lanes_tag, const StreamUnit& u, int task) {
@@ -455,21 +456,27 @@ void decode_stream_kernel(StreamArgs a) {
       }
     }
   };
-  // Counts one part of the unit in; the part that completes it merges.  The part's stores
-  // complete before the count, and the merge's loads issue only after it returned.
-  auto arrive = [&](const StreamUnit& u, int task) {
+  // Flags the part in `slot` complete; a part that then finds all of the task's flags set merges.
+  // Each flag is written (device scope, acknowledged) after the part's own stores and before
+  // it looks, so the part whose flag lands last finds them all; should two find them, both
+  // write the same rows.  Unlike a counter, the flags need no zeros to start from.
+  auto arrive = [&](const StreamUnit& u, int task, int64_t slot) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    int arrived = 0;
     if (lane == 0)
-      arrived = __hip_atomic_fetch_add(a.tickets + (int64_t)head * R + u.w0, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    arrived = __builtin_amdgcn_readfirstlane(arrived);
+      __hip_atomic_store(a.flags + slot, a.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const int np = stream_parts(u, kWaves);
+    for (int e = lane; e - lane < np; e += 64) {
+      const int64_t other = slot0 + stream_slot(u, slots, task, min(e, np - 1));
+      if (__any(__hip_atomic_load(a.flags + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != a.call))
+        return;
+    }
     asm volatile("" ::: "memory");
-    if (arrived != stream_parts(u, kWaves) - 1) return;
     if (G > 4) merge(std::integral_constant<int, 8>(), u, task);
     else merge(std::integral_constant<int, 16>(), u, task);
   };
 
-  if (has_flush) arrive(flush, flush_task);
+  if (has_flush) arrive(flush, flush_task, slot0 + slots.ended(run, flush_task));
   if (!has_final) return;
   auto left_open = [&](int x) { return __builtin_amdgcn_readfirstlane(open_task[x]); };
   if (wave > 0 && left_open(wave - 1) == cu.task) return;  // the first of these waves goes on
@@ -522,13 +529,13 @@ void decode_stream_kernel(StreamArgs a) {
   };
   if (G > 4) combine(std::integral_constant<int, 8>());
   else combine(std::integral_constant<int, 16>());
-  if (!whole) arrive(u, cu.task);
+  if (!whole) arrive(u, cu.task, slot0 + slots.open(run, cu.task));
 }
 
 template <int D, bool kAppend>
 hipError_t launch_stream(const StreamArgs& a, hipStream_t stream) {
   const int waves = stream_waves((int64_t)a.num_runs * a.num_kv_heads);
-  const int blocks = (a.num_runs + waves - 1) / waves * a.num_kv_heads;
+  const int blocks = stream_groups(a.num_runs, a.num_kv_heads);
   if (waves == kStreamBig)
     hipLaunchKernelGGL((decode_stream_kernel<D, kAppend, kStreamBig>), dim3(blocks),
                        dim3(kStreamBig * 64), 0, stream, a);

@@ -225,8 +225,13 @@ void extend_attn_kernel(ExtendArgs a) {
   } else {
     it = a.items[blockIdx.x];
   }
-  if (it.ntok == 0) return;  // padding slot of the XCD-interleaved work list
   const TaskDesc td = a.tasks[it.task];
+  if (!kSplit && a.reads.done) {
+    asm volatile("" ::"v"(it.ntok), "v"(td.extend));  // both records have arrived
+    __syncthreads();
+    if (tid == 0) plan_read(a.reads, blockIdx.x);
+  }
+  if (it.ntok == 0) return;  // padding slot of the XCD-interleaved work list
   const int P = td.prefix;
   const int seq_len = td.prefix + td.extend;
   const int G = a.group;

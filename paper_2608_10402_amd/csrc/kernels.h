@@ -21,5 +21,7 @@ hipError_t launch_decode_stream(const StreamArgs& a, int head_dim, hipStream_t s
 // Waves per workgroup the decode split kernel and the append kernel launch with.
 int decode_waves(int32_t num_items);
 int append_waves();
+// Workgroups of the append kernel per work item.
+int append_groups(int32_t num_kv_heads);
 
 }  // namespace tide

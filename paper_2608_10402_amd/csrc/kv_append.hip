@@ -25,6 +25,11 @@ __global__ __launch_bounds__(kWaves * 64) void kv_append_kernel(AppendArgs a) {
   const AppendItem it = a.items[blockIdx.x];
   const TaskDesc td = a.tasks[it.task];
   const int32_t phys = a.block_table[(int64_t)it.task * a.bt_stride + it.lpage];
+  if (a.reads.done) {
+    asm volatile("" ::"v"(it.pos_end), "v"(td.extend));  // both records have arrived
+    __syncthreads();
+    if (threadIdx.x == 0) plan_read(a.reads, blockIdx.y * gridDim.x + blockIdx.x);
+  }
   const bool page_ok = phys >= 0 && phys < a.num_pages;
   if (!page_ok && threadIdx.x == 0) atomicOr(a.error_flags, 1);
   if (g >= a.num_kv_heads || !page_ok) return;
@@ -63,7 +68,7 @@ __global__ __launch_bounds__(kWaves * 64) void kv_append_kernel(AppendArgs a) {
 
 template <int D>
 hipError_t launch(const AppendArgs& a, hipStream_t stream) {
-  dim3 grid(a.num_items, (a.num_kv_heads + kWaves - 1) / kWaves);
+  dim3 grid(a.num_items, append_groups(a.num_kv_heads));
   hipLaunchKernelGGL((kv_append_kernel<D>), grid, dim3(kWaves * 64), 0, stream, a);
   return hipGetLastError();
 }
@@ -71,6 +76,8 @@ hipError_t launch(const AppendArgs& a, hipStream_t stream) {
 }  // namespace kern
 
 int append_waves() { return kern::kWaves; }
+
+int append_groups(int32_t num_kv_heads) { return (num_kv_heads + kern::kWaves - 1) / kern::kWaves; }
 
 hipError_t launch_kv_append(const AppendArgs& a, hipStream_t stream) {
   if (a.num_items == 0) return hipSuccess;

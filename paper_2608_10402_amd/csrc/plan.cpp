@@ -743,10 +743,10 @@ int make_plan_decode(int32_t num_tasks, const int32_t* kv_lens, const tide_dims&
   off = align_up(off + (size_t)num_tasks * sizeof(TaskDesc), kWsAlign);
   plan->items_off = off;
   off = align_up(off + (size_t)plan->num_runs * sizeof(StreamItem), kWsAlign);
-  plan->tickets_off = off;  // left zero in the blob: every call starts the counts at 0
-  off = align_up(off + (size_t)plan->num_items * sizeof(int32_t), kWsAlign);
-  plan->upload_bytes = off;
   const StreamSlots per_head = {plan->num_runs, num_tasks, stream_waves(plan->num_items)};
+  plan->tickets_off = off;  // the parts' flags, zero in the blob
+  off = align_up(off + (size_t)per_head.count() * hkv * sizeof(uint64_t), kWsAlign);
+  plan->upload_bytes = off;
   const size_t slots = (size_t)per_head.count() * dims.num_q_heads;
   plan->part_o_off = off;
   off = align_up(off + slots * dims.head_dim * sizeof(float), kWsAlign);

@@ -1,6 +1,7 @@
 // The extern "C" entry points declared in include/tide.h: validation and planning on the
-// host (plan.cpp), a copy kernel that moves the work lists from a pinned staging ring
-// into the caller's workspace, then the kernel launches, all on the caller's stream.
+// host (plan.cpp), the work lists staged in a pinned ring, where a small call's kernel reads
+// them and from where a copy kernel moves a larger one's into the caller's workspace, then
+// the kernel launches, all on the caller's stream.
 #include <hip/hip_runtime.h>
 #include <stdlib.h>
 #include <string.h>
@@ -8,9 +9,11 @@
 #include <sched.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <mutex>
 #include <new>
+#include <random>
 #include <vector>
 
 #include "kernels.h"
@@ -27,21 +30,21 @@ constexpr int kStagingSlots = 16;
 // reallocate: freeing and allocating pinned memory is slow and can stall the device.
 constexpr size_t kStagingMin = 2u << 20;
 
-// Pinned, device-mapped host buffers the work lists are staged in.  A kernel on the
-// caller's stream copies a slot into the workspace (no DMA-engine copy, so no hand-off
-// between engines on every call).  A slot is reused only once that copy has read it:
-// each of the copy's workgroups, after all its reads have returned, writes the slot's
-// use count into its own flag in coherent host memory, and the host checks the flags
-// before it overwrites the slot.  (A completion event recorded behind each copy did the
-// same, but delayed the call's next kernel by several microseconds.)
+// Pinned, device-mapped host buffers the work lists are staged in.  The call's own kernel
+// reads a slot in place, or a kernel on the caller's stream copies it into the workspace (no
+// DMA-engine copy, so no hand-off between engines on every call).  A slot is reused only once
+// it has been read: each workgroup of its reader, after all its reads have returned, writes
+// the slot's use count into its own flag in coherent host memory, and the host checks the
+// flags before it overwrites the slot.  (A completion event recorded behind each copy did
+// the same, but delayed the call's next kernel by several microseconds.)
 struct StagingSlot {
   void* host = nullptr;
   const void* dev = nullptr;  // the same memory as seen from the device
   size_t cap = 0;
-  uint32_t* flags = nullptr;  // one per copy workgroup, coherent host memory
+  uint32_t* flags = nullptr;  // one per reading workgroup, coherent host memory
   uint32_t* flags_dev = nullptr;
   uint32_t seq = 0;           // uses of the slot so far
-  uint32_t nblocks = 0;       // workgroups of the last copy
+  uint32_t nblocks = 0;       // workgroups of the last reader
   bool pending = false;
 };
 
@@ -59,8 +62,8 @@ __global__ __launch_bounds__(256) void stage_copy_kernel(u32x4_t* dst, const u32
     __hip_atomic_store(done + blockIdx.x, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Waits until every workgroup of the slot's last copy has set its flag.  Normally the
-// copy finished long ago; if not, this waits like a synchronisation on it would, and
+// Waits until every workgroup of the slot's last reader has set its flag.  Normally it
+// finished long ago; if not, this waits like a synchronisation on it would, and
 // after a few seconds (TIDE_STAGING_WAIT_US microseconds, if set; tests set 0 to take
 // this path) falls back to a device synchronisation (which reports a failed device)
 // before giving up.
@@ -124,7 +127,32 @@ bool debug_checks() {
   return e && e[0] == '1';
 }
 
-int upload(const Plan& plan, void* workspace, hipStream_t stream) {
+// Where a call's kernel finds its plan.
+struct Staged {
+  const uint8_t* plan = nullptr;  // the workspace, or a staging slot
+  PlanReads reads = {nullptr, 0};
+  StagingSlot* slot = nullptr;    // set with reads.done
+};
+
+// A plan that at most this many workgroups read, once each, is read where it was staged: a
+// record costs each a read of host memory (about 2 us), which is less than the copy kernel,
+// its launch and the gap behind it (3-5 us on the GPU and 3 on the host): a four-task decode
+// step went from 16.0 to 13.5 us, the smallest append + extend from 31 to 25.
+constexpr uint32_t kInPlaceGroups = 512;
+
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+// Stages the plan.  readers: the workgroups of the one kernel that reads it, if it may be read
+// in place (0: not).  Under debug checks the kernel needs the zeroed header, and in a captured
+// graph the copy that a replay runs again, so both keep the copy into the workspace.
+int upload(const Plan& plan, void* workspace, hipStream_t stream, uint32_t readers, Staged* out) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0) return TIDE_ERR_HIP;
   std::lock_guard<std::mutex> lock(g_mutex);
@@ -147,7 +175,7 @@ int upload(const Plan& plan, void* workspace, hipStream_t stream) {
     const size_t nflags = cap / kCopyBytesPerBlock + 1;
     void* dev_ptr = nullptr;
     void* flags_dev = nullptr;
-    if (hipHostMalloc(&s.host, cap, hipHostMallocMapped) != hipSuccess ||
+    if (hipHostMalloc(&s.host, cap, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
         hipHostGetDevicePointer(&dev_ptr, s.host, 0) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&s.flags), nflags * sizeof(uint32_t),
                       hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
@@ -162,21 +190,38 @@ int upload(const Plan& plan, void* workspace, hipStream_t stream) {
     s.flags_dev = static_cast<uint32_t*>(flags_dev);
     s.cap = cap;
   }
+  s.seq = s.seq + 1 == 0 ? 1 : s.seq + 1;  // never 0, the flags' initial value
+  if (readers > 0 && readers <= kInPlaceGroups && !debug_checks() && !capturing(stream)) {
+    // (the flags a decode plan ends with need no zeros)
+    memcpy(s.host, plan.blob.data(), plan.stream ? plan.tickets_off : need);
+    s.nblocks = readers;
+    s.pending = true;
+    out->plan = static_cast<const uint8_t*>(s.dev);
+    out->reads = PlanReads{s.flags_dev, s.seq};
+    out->slot = &s;
+    return TIDE_OK;
+  }
   memcpy(s.host, plan.blob.data(), need);
   const size_t n16 = need / 16;
   const uint32_t nblocks = (uint32_t)((n16 + 255) / 256);
-  s.seq = s.seq + 1 == 0 ? 1 : s.seq + 1;  // never 0, the flags' initial value
   hipLaunchKernelGGL(stage_copy_kernel, dim3(nblocks), dim3(256), 0, stream,
                      static_cast<u32x4_t*>(workspace), static_cast<const u32x4_t*>(s.dev), n16,
                      s.flags_dev, s.seq);
   if (hipGetLastError() != hipSuccess) return TIDE_ERR_HIP;
   s.nblocks = nblocks;
   s.pending = true;
+  out->plan = static_cast<const uint8_t*>(workspace);
   return TIDE_OK;
 }
 
-int finish(hipError_t launch_status, void* workspace, hipStream_t stream) {
-  if (launch_status != hipSuccess) return TIDE_ERR_HIP;
+int finish(hipError_t launch_status, const Staged& st, void* workspace, hipStream_t stream) {
+  if (launch_status != hipSuccess) {
+    if (st.slot) {  // nothing will read the slot
+      std::lock_guard<std::mutex> lock(g_mutex);
+      if (st.slot->seq == st.reads.seq) st.slot->pending = false;
+    }
+    return TIDE_ERR_HIP;
+  }
   if (!debug_checks()) return TIDE_OK;
   if (hipStreamSynchronize(stream) != hipSuccess) return TIDE_ERR_HIP;
   int32_t flags = 0;
@@ -186,13 +231,26 @@ int finish(hipError_t launch_status, void* workspace, hipStream_t stream) {
 }
 
 template <class T>
-const T* at(void* ws, size_t off) {
-  return reinterpret_cast<const T*>(static_cast<uint8_t*>(ws) + off);
+const T* at(const void* ws, size_t off) {
+  return reinterpret_cast<const T*>(static_cast<const uint8_t*>(ws) + off);
 }
 
 template <class T>
 T* at_mut(void* ws, size_t off) {
   return reinterpret_cast<T*>(static_cast<uint8_t*>(ws) + off);
+}
+
+// A number no other call of the process has, and no chance contents of a workspace: the count
+// starts at a random 64-bit number.
+uint64_t next_call() {
+  static std::atomic<uint64_t> count([] {
+    std::random_device r;
+    return ((uint64_t)r() << 32) ^ r();
+  }());
+  uint64_t c;
+  do c = count.fetch_add(1, std::memory_order_relaxed);
+  while (c == 0);  // what a copied plan zeroes the flags to
+  return c;
 }
 
 // Shared path of tide_extend_attn and tide_full_prefill_attn.
@@ -216,9 +274,11 @@ int run_extend(int op, const void* q, const void* k_pool, const void* v_pool, in
   if (fused && (!k_new || !v_new)) return TIDE_ERR_INVALID_ARG;
   if (workspace_bytes < plan.total_bytes) return TIDE_ERR_CAPACITY;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  rc = upload(plan, workspace, s);
+  Staged st;
+  rc = upload(plan, workspace, s, plan.split ? 0 : (uint32_t)plan.num_items, &st);
   if (rc != TIDE_OK) return rc;
   ExtendArgs a;
+  a.reads = st.reads;
   a.k_new = fused ? static_cast<const uint16_t*>(k_new) : nullptr;
   a.v_new = fused ? static_cast<const uint16_t*>(v_new) : nullptr;
   a.q = static_cast<const uint16_t*>(q);
@@ -232,8 +292,8 @@ int run_extend(int op, const void* q, const void* k_pool, const void* v_pool, in
   a.group = dims->num_q_heads / dims->num_kv_heads;
   a.scale_log2 = dims->sm_scale * 1.44269504088896340736f;
   a.num_items = plan.num_items;
-  a.tasks = at<TaskDesc>(workspace, plan.tasks_off);
-  a.items = plan.split ? nullptr : at<ExtendItem>(workspace, plan.items_off);
+  a.tasks = at<TaskDesc>(st.plan, plan.tasks_off);
+  a.items = plan.split ? nullptr : at<ExtendItem>(st.plan, plan.items_off);
   a.out = static_cast<uint16_t*>(out);
   a.lse = lse;
   a.error_flags = at_mut<int32_t>(workspace, 0);
@@ -242,7 +302,7 @@ int run_extend(int op, const void* q, const void* k_pool, const void* v_pool, in
   a.part_o = plan.split ? at_mut<float>(workspace, plan.part_o_off) : nullptr;
   a.part_ml = plan.split ? at_mut<float>(workspace, plan.part_ml_off) : nullptr;
   a.total_rows = plan.total_rows;
-  return finish(launch_extend(a, dims->head_dim, plan.waves, s), workspace, s);
+  return finish(launch_extend(a, dims->head_dim, plan.waves, s), st, workspace, s);
 }
 
 // Shared path of tide_decode_attn, tide_decode_append_attn (fused: k_new / v_new) and
@@ -266,6 +326,7 @@ int run_decode(const void* q, const void* k_new, const void* v_new, const void* 
   if (!q || !k_pool || !v_pool || !block_table || !out) return TIDE_ERR_INVALID_ARG;
   if (fused && (!k_new || !v_new)) return TIDE_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  Staged st;
   if (in_scratch) {
     if (plan.total_bytes > (size_t)TIDE_NOALLOC_SCRATCH_BYTES) return TIDE_ERR_CAPACITY;
     rc = scratch_address(&workspace);
@@ -274,10 +335,16 @@ int run_decode(const void* q, const void* k_new, const void* v_new, const void* 
     if (hipMemcpyAsync(workspace, plan.blob.data(), plan.blob.size(), hipMemcpyHostToDevice, s) !=
         hipSuccess)
       return TIDE_ERR_HIP;
+    st.plan = static_cast<const uint8_t*>(workspace);
   } else {
     if (!workspace) return TIDE_ERR_INVALID_ARG;
     if (workspace_bytes < plan.total_bytes) return TIDE_ERR_CAPACITY;
-    rc = upload(plan, workspace, s);
+    // a wave reads the task table again where its run crosses into the next task, so a call
+    // with more tasks than runs keeps the copy
+    const uint32_t readers = plan.stream && num_tasks <= plan.num_runs
+                                 ? stream_groups(plan.num_runs, dims->num_kv_heads)
+                                 : 0;
+    rc = upload(plan, workspace, s, readers, &st);
     if (rc != TIDE_OK) return rc;
   }
   if (plan.stream) {
@@ -296,17 +363,19 @@ int run_decode(const void* q, const void* k_new, const void* v_new, const void* 
     a.num_tasks = num_tasks;
     a.steps = plan.steps;
     a.last_steps = plan.last_steps;
-    a.tasks = at<TaskDesc>(workspace, plan.tasks_off);
-    a.items = at<StreamItem>(workspace, plan.items_off);
+    a.tasks = at<TaskDesc>(st.plan, plan.tasks_off);
+    a.items = at<StreamItem>(st.plan, plan.items_off);
+    a.reads = st.reads;
     a.part_o = at_mut<float>(workspace, plan.part_o_off);
     a.part_ml = at_mut<float>(workspace, plan.part_ml_off);
-    a.tickets = at_mut<int32_t>(workspace, plan.tickets_off);
+    a.flags = at_mut<uint64_t>(workspace, plan.tickets_off);
+    a.call = next_call();
     a.out = static_cast<uint16_t*>(out);
     a.lse = lse;
     a.error_flags = at_mut<int32_t>(workspace, 0);
     a.k_new = static_cast<const uint16_t*>(k_new);
     a.v_new = static_cast<const uint16_t*>(v_new);
-    return finish(launch_decode_stream(a, dims->head_dim, s), workspace, s);
+    return finish(launch_decode_stream(a, dims->head_dim, s), st, workspace, s);
   }
   DecodeArgs a;
   a.q = static_cast<const uint16_t*>(q);
@@ -333,7 +402,7 @@ int run_decode(const void* q, const void* k_new, const void* v_new, const void* 
   a.k_new = static_cast<const uint16_t*>(k_new);
   a.v_new = static_cast<const uint16_t*>(v_new);
   a.tickets = plan.fold_merge ? at_mut<int32_t>(workspace, plan.tickets_off) : nullptr;
-  return finish(launch_decode(a, dims->head_dim, false, s), workspace, s);
+  return finish(launch_decode(a, dims->head_dim, false, s), st, workspace, s);
 }
 
 }  // namespace
@@ -414,9 +483,12 @@ TIDE_API int tide_kv_append(const void* k_new, const void* v_new, void* k_pool, 
       return TIDE_ERR_INVALID_ARG;
     if (workspace_bytes < plan.total_bytes) return TIDE_ERR_CAPACITY;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    rc = upload(plan, workspace, s);
+    Staged st;
+    const int64_t groups = (int64_t)plan.num_items * append_groups(dims->num_kv_heads);
+    rc = upload(plan, workspace, s, groups <= kInPlaceGroups ? (uint32_t)groups : 0, &st);
     if (rc != TIDE_OK) return rc;
     AppendArgs a;
+    a.reads = st.reads;
     a.k_new = static_cast<const uint16_t*>(k_new);
     a.v_new = static_cast<const uint16_t*>(v_new);
     a.k_pool = static_cast<uint16_t*>(k_pool);
@@ -427,10 +499,10 @@ TIDE_API int tide_kv_append(const void* k_new, const void* v_new, void* k_pool, 
     a.num_kv_heads = dims->num_kv_heads;
     a.head_dim = dims->head_dim;
     a.num_items = plan.num_items;
-    a.tasks = at<TaskDesc>(workspace, plan.tasks_off);
-    a.items = at<AppendItem>(workspace, plan.items_off);
+    a.tasks = at<TaskDesc>(st.plan, plan.tasks_off);
+    a.items = at<AppendItem>(st.plan, plan.items_off);
     a.error_flags = at_mut<int32_t>(workspace, 0);
-    return finish(launch_kv_append(a, s), workspace, s);
+    return finish(launch_kv_append(a, s), st, workspace, s);
   } catch (...) {
     return TIDE_ERR_HIP;
   }
@@ -564,7 +636,8 @@ TIDE_API int tide_decode_attn_shared(const void* q, const void* k_pool, const vo
       return TIDE_ERR_INVALID_ARG;
     if (workspace_bytes < plan.total_bytes) return TIDE_ERR_CAPACITY;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    rc = upload(plan, workspace, s);
+    Staged st;
+    rc = upload(plan, workspace, s, 0, &st);
     if (rc != TIDE_OK) return rc;
     DecodeArgs a;
     a.q = static_cast<const uint16_t*>(q);
@@ -591,7 +664,7 @@ TIDE_API int tide_decode_attn_shared(const void* q, const void* k_pool, const vo
     a.k_new = nullptr;
     a.v_new = nullptr;
     a.tickets = nullptr;
-    return finish(launch_decode(a, dims->head_dim, true, s), workspace, s);
+    return finish(launch_decode(a, dims->head_dim, true, s), st, workspace, s);
   } catch (...) {
     return TIDE_ERR_HIP;
   }

@@ -110,6 +110,12 @@ TIDE_HD inline StreamUnit stream_unit(int32_t w, int32_t begin, int32_t part, in
 // waves takes 4, so that it spreads over more CUs.
 TIDE_HD inline int32_t stream_waves(int64_t items) { return items > 256 ? 8 : 4; }
 
+// Workgroups of such a call.
+TIDE_HD inline int32_t stream_groups(int32_t runs, int32_t num_kv_heads) {
+  const int32_t waves = stream_waves((int64_t)runs * num_kv_heads);
+  return (runs + waves - 1) / waves * num_kv_heads;
+}
+
 // Where the partials of one kv head's cut tasks go.  The parts that reach their run's end are
 // combined per workgroup, into one slot for each (workgroup, task); a part that ends inside
 // its run has a slot of its own, at most one for a task and one for a run.  Along the runs
@@ -171,6 +177,14 @@ struct WsHeader {
   int32_t pad[63];
 };
 
+// A plan (tasks, items) that the kernel reads in place in a pinned staging slot: each workgroup
+// sets done[its index] to seq once it has read all it will read of it, and the host then
+// reuses the slot.  done == nullptr: the plan is in the workspace.
+struct PlanReads {
+  uint32_t* done;
+  uint32_t seq;
+};
+
 struct AppendArgs {
   const uint16_t* k_new;
   const uint16_t* v_new;
@@ -185,6 +199,7 @@ struct AppendArgs {
   const TaskDesc* tasks;
   const AppendItem* items;
   int32_t* error_flags;
+  PlanReads reads;
 };
 
 struct ExtendArgs {
@@ -217,6 +232,7 @@ struct ExtendArgs {
   // pool, and each item writes its own tokens' rows into the pool.
   const uint16_t* k_new;
   const uint16_t* v_new;
+  PlanReads reads;  // (plain plan)
 };
 
 struct DecodeArgs {
@@ -274,13 +290,16 @@ struct StreamArgs {
   float* part_o;     // [Hkv][slots][group][d] unnormalised outputs
   float* part_ml;    // [Hkv][slots][group][4]: max (base-2 units), sum of the bf16-rounded
                      // weights, exact fp32 sum, unused
-  int32_t* tickets;  // [Hkv][num_runs] arrivals of the task whose first part run w holds, zero
-                     // at launch
+  // one flag per partial slot: this call's number once the partial is complete (whatever an
+  // earlier use of the workspace left there is another call's)
+  uint64_t* flags;
+  uint64_t call;
   uint16_t* out;
   float* lse;
   int32_t* error_flags;
   const uint16_t* k_new;  // fused append as in DecodeArgs
   const uint16_t* v_new;
+  PlanReads reads;
 };
 
 }  // namespace tide

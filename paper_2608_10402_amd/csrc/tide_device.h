@@ -69,6 +69,12 @@ __device__ __forceinline__ float xor_shfl(float v, int mask) {
   return __shfl_xor(v, mask, 64);
 }
 
+// Tells the host that workgroup `group` has read its part of a plan in a staging slot.  One
+// thread calls it, after a barrier behind which every wave has its plan values.
+__device__ __forceinline__ void plan_read(const PlanReads& r, uint32_t group) {
+  __hip_atomic_store(r.done + group, r.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Merge of split partials, the split-K merge of flash decoding.  D / 4 lanes combine the n
 // partials of one (row, query head), so a wave takes 64 / (D / 4) of them (kMergeRows): partial s holds, at
 // ml + s * ml_stride, its running max m_s (base-2 units), the sum of its bf16-rounded weights

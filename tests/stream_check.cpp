@@ -5,8 +5,8 @@
 //   * the runs tile the tasks' steps in order, and each record names its run's first step;
 //   * every cut task's parts, as each of its waves derives them, agree; the slots written
 //     are distinct, in bounds, the ones the merge reads, and in key order; and as many parts
-//     arrive at the task's counter as the merge waits for;
-//   * the workspace regions lie in order, the counters zero in the upload.
+//     are flagged as the merge waits for;
+//   * the workspace regions lie in order, the flags zero in the upload.
 #include <stdio.h>
 
 #include <algorithm>
@@ -45,20 +45,20 @@ static int check(const tide_dims& dims, const std::vector<int32_t>& kv) {
   if (plan.num_runs < 1 || plan.num_items != plan.num_runs * hkv ||
       plan.num_items > std::max(2048, hkv))
     return fail("waves", plan.num_items);
-  const size_t W = plan.num_items, R = plan.num_runs;
+  const size_t R = plan.num_runs;
   const int per = stream_waves(plan.num_items);
   const StreamSlots sl = {plan.num_runs, n, per};
   const size_t slots = sl.count();
   std::map<int, int> used;  // slot -> task
   if (plan.items_off < plan.tasks_off + n * sizeof(TaskDesc) ||
       plan.tickets_off < plan.items_off + R * sizeof(StreamItem) ||
-      plan.upload_bytes < plan.tickets_off + 4 * W || plan.blob.size() != plan.upload_bytes ||
+      plan.upload_bytes < plan.tickets_off + 8 * slots * hkv || plan.blob.size() != plan.upload_bytes ||
       plan.part_o_off < plan.upload_bytes ||
       plan.part_ml_off < plan.part_o_off + slots * hkv * G * dims.head_dim * 4 ||
       plan.total_bytes < plan.part_ml_off + slots * hkv * G * 16)
     return fail("layout");
-  for (size_t i = 0; i < 4 * W; ++i)
-    if (plan.blob[plan.tickets_off + i]) return fail("counter not zero", (long)i);
+  for (size_t i = plan.tickets_off; i < plan.upload_bytes; ++i)
+    if (plan.blob[i]) return fail("flag not zero", (long)i);
   const TaskDesc* tasks = (const TaskDesc*)(plan.blob.data() + plan.tasks_off);
   const StreamItem* items = (const StreamItem*)(plan.blob.data() + plan.items_off);
   std::map<int, Seen> cut;
