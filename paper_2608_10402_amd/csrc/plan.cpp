@@ -56,6 +56,7 @@ constexpr int64_t kDecodeMinChunk = 512;
 constexpr int64_t kDecodeMaxChunk = 16384;
 constexpr int64_t kDecodeTargetItems = 4096;
 constexpr int64_t kStreamMaxSteps = 208;  // longest run of the equal-runs plan
+constexpr int64_t kStreamMergeSteps = 40;  // see make_plan_decode
 constexpr int64_t kFoldMeanSplits = 4;  // merge inside the split kernel up to this mean
 
 // The automatic decode chunk (see kDecodeRoundCost).  Round rule: for R rounds from the
@@ -704,6 +705,11 @@ int make_plan(int op, int32_t num_tasks, const int32_t* lens_a, const int32_t* l
 // memory.  Measured on MI355X (call us, chunks against runs): 190 steps 1013 / 957, 187 steps
 // 945 / 928, 225 steps (256 tasks of 1k-32k, 32 / 8 heads) 1140 / 1141, 246 steps (32 of
 // 32k-96k, 64 / 8 heads) 1214 / 1248.
+// With few kv heads a task has many runs, and the one wave that merges its parts (a batch of loads
+// after the other, 0.25 us a part) outlasts short runs (0.6 us a step): the sum of both is least
+// where steps^2 is in proportion to the task's length.  One task of 60,000 keys (1875 steps), 32 /
+// 2 heads, d = 64: 2 steps a run 46.2 us, 3 35.5, 4 31.7, 6 27.5, 8 28.9, 16 29.3 (chunks 28.0);
+// 30,000 keys, 8 / 2 heads: 1 step 24.1, 2 17.5, 4 16.3, 6 18.4, 12 19.7 (chunks 24.1).
 int make_plan_decode(int32_t num_tasks, const int32_t* kv_lens, const tide_dims& dims,
                      int32_t num_splits, int32_t bt_stride, bool build_blob, Plan* plan) {
   if (!plan || num_tasks < 0 || num_splits < 0) return TIDE_ERR_INVALID_ARG;
@@ -721,7 +727,8 @@ int make_plan_decode(int32_t num_tasks, const int32_t* kv_lens, const tide_dims&
     longest = std::max(longest, st);
   }
   const int32_t hkv = dims.num_kv_heads;
-  const int64_t steps = ceil_div(total, std::max<int64_t>(1, kDecodeWaveSlots / hkv));
+  int64_t steps = ceil_div(total, std::max<int64_t>(1, kDecodeWaveSlots / hkv));
+  while (kStreamMergeSteps * (steps + 1) * (steps + 1) <= longest) ++steps;
   if (steps > kStreamMaxSteps)
     return make_plan(TIDE_OP_DECODE, num_tasks, kv_lens, nullptr, dims, num_splits, bt_stride,
                      build_blob, plan);
