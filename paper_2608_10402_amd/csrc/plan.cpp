@@ -57,6 +57,8 @@ constexpr int64_t kDecodeMaxChunk = 16384;
 constexpr int64_t kDecodeTargetItems = 4096;
 constexpr int64_t kStreamMaxSteps = 208;  // longest run of the equal-runs plan
 constexpr int64_t kStreamMergeSteps = 40;  // see make_plan_decode
+// Shared-prefix decode in one round of waves: chunks of at most this length.
+constexpr int64_t kSharedRoundChunk = 1280;
 constexpr int64_t kFoldMeanSplits = 4;  // merge inside the split kernel up to this mean
 
 // The automatic decode chunk (see kDecodeRoundCost).  Round rule: for R rounds from the
@@ -810,23 +812,47 @@ int make_plan_shared(int32_t num_tasks, const int32_t* kv_lens, int32_t num_grou
   }
   plan->total_rows = num_tasks;
 
-  // Chunk length: the same rule as decode, counting a shared prefix once per item group.
   int64_t chunk = 0;
   if (num_splits > 0) {
     for (int32_t b = 0; b < num_tasks; ++b)
       chunk = std::max<int64_t>(chunk, ceil_div(kv_lens[b], num_splits));
     chunk = std::max<int64_t>(kDecodeStep, ceil_div(chunk, kDecodeStep) * kDecodeStep);
   } else {
-    int64_t total = 0;
-    for (int32_t g = 0; g < (num_tasks > 0 ? num_groups : 0); ++g) {
-      const int32_t n = group_start[g + 1] - group_start[g];
-      total += ceil_div(n, per_item) * (int64_t)shared_lens[g];
+    // One round of waves, if chunks of at most kSharedRoundChunk keys can be that few: the
+    // shortest that are.  Otherwise the item rule of decode, counting a shared prefix once per
+    // item group.  Measured on MI355X (call us, item rule against one round of the chunk named):
+    // 32 tasks in groups of 4, prompts of 2k-6k and 2k-16k keys of their own (32 / 8 heads) 167 /
+    // 154 at 992; 64 in groups of 8, 4k-6k and 0.5k-4k (8 / 8) 122 / 102 at 672; 80 in groups of
+    // 4, 4k-8k and 0.3k-4k (32 / 8) 173 / 165 at 1056.  Longer ones gain less for the shape's
+    // raggedness: 181 / 177 at 1344, 212 / 210 at 1504, 156 / 160 at 1536 (64 / 8, 80 tasks).
+    auto items_at = [&](int64_t c) {
+      int64_t n = 0;
+      for (int32_t g = 0; g < (num_tasks > 0 ? num_groups : 0); ++g)
+        n += ceil_div(group_start[g + 1] - group_start[g], per_item) * ceil_div(shared_lens[g], c);
+      for (int32_t b = 0; b < num_tasks; ++b) n += ceil_div((int64_t)kv_lens[b] - shared_of[b], c);
+      return n * dims.num_kv_heads;
+    };
+    if (items_at(kSharedRoundChunk) <= kDecodeWaveSlots) {
+      int64_t lo = kDecodeMinChunk / kDecodeStep, hi = kSharedRoundChunk / kDecodeStep;
+      if (items_at(kDecodeMinChunk) <= kDecodeWaveSlots) hi = lo;
+      while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) / 2;
+        if (items_at(mid * kDecodeStep) <= kDecodeWaveSlots) hi = mid;
+        else lo = mid;
+      }
+      chunk = hi * kDecodeStep;
+    } else {
+      int64_t total = 0;
+      for (int32_t g = 0; g < (num_tasks > 0 ? num_groups : 0); ++g) {
+        const int32_t n = group_start[g + 1] - group_start[g];
+        total += ceil_div(n, per_item) * (int64_t)shared_lens[g];
+      }
+      for (int32_t b = 0; b < num_tasks; ++b) total += (int64_t)kv_lens[b] - shared_of[b];
+      total *= dims.num_kv_heads;
+      chunk = ceil_div(total, kDecodeTargetItems);
+      chunk = ceil_div(chunk, kDecodeStep) * kDecodeStep;
+      chunk = std::min<int64_t>(std::max<int64_t>(chunk, kDecodeMinChunk), kDecodeMaxChunk);
     }
-    for (int32_t b = 0; b < num_tasks; ++b) total += (int64_t)kv_lens[b] - shared_of[b];
-    total *= dims.num_kv_heads;
-    chunk = ceil_div(total, kDecodeTargetItems);
-    chunk = ceil_div(chunk, kDecodeStep) * kDecodeStep;
-    chunk = std::min<int64_t>(std::max<int64_t>(chunk, kDecodeMinChunk), kDecodeMaxChunk);
   }
 
   std::vector<SharedDecodeItem> items;
