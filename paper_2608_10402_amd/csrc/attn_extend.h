@@ -38,8 +38,8 @@
 //     lanes of an operand read hit distinct banks.
 //   * Scores stay raw until one FMA applies sm_scale*log2(e) and subtracts the running
 //     max before v_exp_f32.  A row's reference is the maximum of its first tile and is only
-//     raised when a tile's weights outgrow it by far (kTileSumMax), so later tiles need no
-//     maximum and the O rescale is skipped on almost every one.
+//     raised when a tile's weights outgrow it (kTileSumMax), so later tiles need no
+//     maximum and the O rescale is skipped on most of them.
 //   * Causal masking is applied only on tiles that cross the diagonal.  On the last
 //     tile, V operands of key slots at or beyond the task's length are zeroed in
 //     registers, so NaN/Inf garbage in unused pool slots can never reach the output.
@@ -88,10 +88,14 @@ __device__ __forceinline__ void dma16_lane(const void* src, uint8_t* lds) {
   __builtin_amdgcn_global_load_lds((glb_void*)src, (lds_void*)lds, 16, 0, 0);
 }
 
-// A tile's weights are kept as evaluated against the row's reference unless their sum
-// exceeds this: weights then stay below 2^30, and the sums of 2^31 keys times values of up
-// to 2^60 stay inside fp32's range.
-constexpr float kTileSumMax = 1073741824.0f;  // 2^30
+// A tile's weights are kept as evaluated against the row's reference while a lane's share of
+// their sum (32 keys) is below this, so no weight reaches 2^kRescaleSlack and every tile whose
+// maximum exceeds the reference by more than that raises it.  The largest weight of a row is
+// rounded to bf16 unless its key is the reference (2^0 = 1 is exact), and larger weights leave
+// V less of fp32's range, so the bound is no higher than decode's: with 2^30 here, 16 tasks of
+// 4k-24k keys, a tenth of them scaled by 4, were 14% further from the exact result before the
+// output's own rounding (rms 9.1e-4 against 8.4e-4 with 2^8 or with a maximum per tile).
+constexpr float kTileSumMax = 256.0f;  // 2^kRescaleSlack
 
 // Physical position of 16-byte granule g of K tile row r.
 template <int D>
@@ -487,11 +491,14 @@ void extend_attn_kernel(ExtendArgs a) {
       __attribute__((always_inline)) {
     float t0, t1;
     lane_pair(lt, t0, t1);
-    const bool over = !(t0 <= kTileSumMax) || !(t1 <= kTileSumMax);
-    float mt = s[0][0];
+    const bool over = !(t0 < kTileSumMax) || !(t1 < kTileSumMax);
+    float mc[4], x0, x1;  // four chains, as in the first tile
 #pragma unroll
-    for (int f = 1; f < 32; ++f) mt = max3(mt, s[f >> 4][f & 15], s[f >> 4][f & 15]);
-    float x0, x1;
+    for (int c = 0; c < 4; ++c) {
+      auto e = [&](int f) { return s[c >> 1][8 * (c & 1) + f]; };
+      mc[c] = max3(max3(max3(e(0), e(1), e(2)), e(3), e(4)), e(5), max3(e(6), e(7), e(7)));
+    }
+    float mt = max3(max3(mc[0], mc[1], mc[2]), mc[3], mc[3]);
     lane_pair(mt, x0, x1);
     mt = max3(x0, x1, x1) * csc;
     const float m_new = over && mt > m_ref ? mt : m_ref;
@@ -532,16 +539,18 @@ void extend_attn_kernel(ExtendArgs a) {
   //
   // Only the first tile (no P.V) takes its maximum before its exponentials.  Every later
   // tile evaluates them against the reference the row already has and is checked
-  // afterwards, by its row sum: below kTileSumMax no weight came near the range of bf16 or
-  // fp32, and being far above 1 costs no precision in either.  A row whose sum is not below
-  // it (or is NaN) has its reference raised to the tile's maximum and the tile evaluated
-  // again (`redo`).  That takes 19 v_max3, the lane exchange, the reference update and its
-  // exponential out of every tile's 129 vector instructions, the maximum out of the chain
-  // from S to P, and every spill out of the plain kernel (it held 45-50 spilled VGPRs).  The
-  // kernel is bound by vector issue and by the card's power limit (the same launch over
-  // zeros runs 1.3x faster), so fewer instructions help twice: 64 tasks of 2k-16k keys and
-  // 64-2,048 new tokens (28 / 4 heads, d = 128) 4.06 -> 3.88 ms, 16 re-prefills of 2k-16k
-  // 9.98 -> 9.37 ms, image-sized extends with the log-sum-exp 6.71 -> 6.21 ms.
+  // afterwards, by its row sum: below kTileSumMax no key outgrew the reference by more than
+  // the slack that decode allows too.  A row whose sum is not below it (or is NaN) has its
+  // reference raised to the tile's maximum and the tile evaluated again (`redo`).  That
+  // takes 19 v_max3, the lane exchange, the reference update and its exponential out of
+  // every tile's 129 vector instructions, the maximum out of the chain from S to P, and
+  // every spill out of the plain kernel (it held 45-50 spilled VGPRs).  The kernel is bound
+  // by vector issue and by the card's power limit (the same launch over zeros runs 1.3x
+  // faster), so fewer instructions help twice: 64 tasks of 2k-16k keys and 64-2,048 new
+  // tokens (28 / 4 heads, d = 128) 4.06 -> 3.88 ms, 16 re-prefills of 2k-16k 9.98 -> 9.37 ms.
+  // Where scores grow along the context the second evaluations take the gain back: with a
+  // tenth of the keys scaled by 4, one of a workgroup's 8 waves raises a reference on about
+  // half of the tiles, and 16 image-sized extends with the log-sum-exp went 6.82 -> 6.94 ms.
   //
   // The operand reads of the next step's first kAhead MFMAs (P.V of this step's tile,
   // from vb_next) are issued in this step's last slots, into pre_next, before the barrier
@@ -683,7 +692,7 @@ void extend_attn_kernel(ExtendArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     });
     if constexpr (kPV) {
-      if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(lt[0] <= kTileSumMax)) != 0, 0))
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(lt[0] < kTileSumMax)) != 0, 0))
         redo(s, pcur, lt[0], le[0]);
     }
     l_part += lt[0];

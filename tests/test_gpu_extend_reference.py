@@ -1,7 +1,7 @@
 """Rows whose score scale jumps after their first key tile (needs an MI355X).
 
 The extend kernel takes a row's softmax reference from its first 64-key tile and raises it
-only when a later tile's weights outgrow it by far.  Here single keys of later tiles are
+only when a later tile's weights outgrow it.  Here single keys of later tiles are
 scaled so that the scores jump by hundreds (base 2), up and down, in some rows of a wave and
 not in others: in unmasked tiles, on the diagonal, in the first and later chunks of a
 split-KV call, and through the fused append.  A softmax over such scores is close to one-hot
@@ -66,6 +66,61 @@ def test_score_jumps(name, split, monkeypatch):
     tol = 1e-3 + 1e-6 * float(np.abs(ref_lse).max())
     assert_lse(lse, ref_lse, "%s fused" % name, tol)
     assert torch.equal(kv.extend(q, [p], [e]), fused)
+
+
+@pytest.mark.parametrize("split", ["0", "1"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_large_values_stay_finite(d, split, monkeypatch):
+    """V of about 2^106 over rows whose scores jump by 0 to 60 (base 2) after their first tile.
+    The weights a row keeps are below 2^8, so its sums stay below 2^121; the outputs are V's
+    size, and their error relative to it is the usual one."""
+    monkeypatch.setenv("TIDE_EXTEND_SPLIT", split)
+    p, e = 400, 60
+    log("large values d %d split %s" % (d, split))
+    kv, q, kn, vn, ref, _ = build(8, 2, d, p, e, {150: 12.0, 333: 16.0}, seed=d)
+    kv.v_pool.mul_(2.0 ** 106)
+    out = kv.extend_append(q, kn, vn * 2.0 ** 106, [p], [e])
+    assert_close(out.double() * 2.0 ** -106, ref, "large values")
+
+
+@pytest.mark.parametrize("lse", [False, True])
+def test_dominant_weight_is_exact(lse):
+    """Two keys of a later tile that outgrow the first by 10 to 40 (base 2), nearly equal, with
+    opposite V.  The larger is the row's reference, so its weight is exactly 1 and only the
+    other's is rounded to bf16; were both rounded, the error would be 1.4 times as large.  The
+    bound is the error of that arithmetic in 64 bits over the same rows (about 1,000, each
+    with an independent rounding: 5% of noise), times 1.15."""
+    hq, hkv, d, p, e = 8, 1, 128, 250, 600
+    g = torch.Generator().manual_seed(5)
+    q = torch.randn((e, hq, d), generator=g).bfloat16()
+    k = torch.randn((p + e, hkv, d), generator=g)
+    v = torch.randn((p + e, hkv, d), generator=g).bfloat16()
+    a, b = 130, 157
+    k[a] *= 12
+    k[b] = k[a] + 0.1 * torch.randn((hkv, d), generator=g)
+    k = k.bfloat16()
+    v[a], v[b] = 1.0, -1.0
+    bt = np.random.default_rng(1).permutation(-(-(p + e) // 16)).astype(np.int32).reshape(1, -1)
+    kv = tide.PagedKV(bt.size, hq, hkv, d, bt)
+    kv.append(k[:p].cuda(), v[:p].cuda(), [0], [p])
+    buf = torch.empty((e, hq), dtype=torch.float32, device="cuda") if lse else None
+    out = kv.extend_append(q.cuda(), k[p:].cuda(), v[p:].cuda(), [p], [e], lse=buf)
+
+    x = q.double().view(e * hq, d) @ k.double().view(-1, d).t() / d ** 0.5 * np.log2(np.e)
+    seen = torch.arange(p + e) <= torch.arange(p, p + e).repeat_interleave(hq)[:, None]
+    x = x.masked_fill(~seen, -np.inf)
+    top = x[:, [a, b]].min(1).values - x[:, :64].max(1).values
+    rows = (top > 10) & (top < 40) & (x.argmax(1) // 64 == a // 64)
+    x = x[rows] - x[rows].max(1, keepdim=True).values
+    w = torch.exp2(x)
+    vd = v.double().view(-1, d)
+    ref = w @ vd / w.sum(1, keepdim=True)
+    w = w.bfloat16().double()
+    model = (w @ vd / w.sum(1, keepdim=True)).bfloat16().double()
+    got = out.double().cpu().view(e * hq, d)[rows]
+    err, bound = (((t - ref) ** 2).mean().sqrt().item() for t in (got, model))
+    log("dominant weight: %d rows, rms error %.3e, of the exact reference %.3e" % (rows.sum(), err, bound))
+    assert rows.sum() > 800 and err <= 1.15 * bound
 
 
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
