@@ -75,6 +75,11 @@
  * small call's kernel reads its work list, and from which a copy kernel on `stream` moves
  * a larger one's into the workspace.  Calls that
  * take a workspace are thread-safe when each call in flight has its own workspace.
+ *
+ * A call on a stream under HIP graph capture puts its work list into the graph (as kernel
+ * arguments, 3,840 bytes a launch), so the graph may be replayed any number of times,
+ * whatever other calls are made in between, for as long as its buffers and workspace live.
+ * The lengths are those of the captured call.
  */
 #ifndef TIDE_H_
 #define TIDE_H_
@@ -249,8 +254,8 @@ TIDE_API int tide_decode_append_attn(const void* q, const void* k_new, const voi
  * TIDE_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on until the
  * process ends.  A call whose tide_workspace_size(TIDE_OP_DECODE, ...) exceeds that
  * returns TIDE_ERR_CAPACITY before any device work.  The work list is copied into the
- * array with hipMemcpyAsync from pageable host memory, so the call may wait for work
- * already queued on `stream`.  Every call on one GPU uses the same array: two calls in
+ * array with hipMemcpyAsync from pageable host memory (not under capture, see above), so the
+ * call may wait for work already queued on `stream`.  Every call on one GPU uses the same array: two calls in
  * flight at once on one GPU (on different streams, or from different threads) race and
  * give undefined results; serialize them on one stream.
  */

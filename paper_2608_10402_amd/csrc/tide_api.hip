@@ -1,7 +1,8 @@
 // The extern "C" entry points declared in include/tide.h: validation and planning on the
 // host (plan.cpp), the work lists staged in a pinned ring, where a small call's kernel reads
-// them and from where a copy kernel moves a larger one's into the caller's workspace, then
-// the kernel launches, all on the caller's stream.
+// them and from where a copy kernel moves a larger one's into the caller's workspace (under
+// graph capture they go there as kernel arguments), then the kernel launches, all on the
+// caller's stream.
 #include <hip/hip_runtime.h>
 #include <stdlib.h>
 #include <string.h>
@@ -60,6 +61,49 @@ __global__ __launch_bounds__(256) void stage_copy_kernel(u32x4_t* dst, const u32
   __syncthreads();
   if (threadIdx.x == 0)
     __hip_atomic_store(done + blockIdx.x, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The same from the kernel's own arguments, which a captured graph holds a copy of.
+constexpr uint32_t kPutWords = 240;  // 16 bytes each; a kernel's arguments hold up to 4 KB
+struct PutArgs {
+  u32x4_t* dst;
+  uint32_t n16;
+  u32x4_t data[kPutWords];
+};
+
+__global__ __launch_bounds__(256) void put_kernel(PutArgs a) {
+  if (threadIdx.x < a.n16) a.dst[threadIdx.x] = a.data[threadIdx.x];
+}
+
+__global__ __launch_bounds__(256) void zero_kernel(u32x4_t* dst, uint32_t n16) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n16) dst[i] = u32x4_t{0u, 0u, 0u, 0u};
+}
+
+// Moves the plan into the workspace for a call under graph capture: as kernel arguments, 3,840
+// bytes a launch, so that a replay needs nothing of the library's or the host's memory (a
+// staging slot would hold a later call's plan by then).  The zeros a decode plan ends with are
+// one launch.  A replay runs 3 such launches for 8 tasks' decode, 17 for 64 agents' extend.
+int put_plan(const Plan& plan, void* workspace, hipStream_t stream) {
+  const size_t need = plan.blob.size();  // a multiple of kWsAlign
+  const size_t filled = plan.tickets_off ? plan.tickets_off : need;
+  uint8_t* ws = static_cast<uint8_t*>(workspace);
+  PutArgs a;
+  for (size_t off = 0; off < filled; off += sizeof(a.data)) {
+    const size_t bytes = std::min(sizeof(a.data), filled - off);
+    a.dst = reinterpret_cast<u32x4_t*>(ws + off);
+    a.n16 = (uint32_t)(bytes / 16);
+    memcpy(a.data, plan.blob.data() + off, bytes);
+    hipLaunchKernelGGL(put_kernel, dim3(1), dim3(256), 0, stream, a);
+    if (hipGetLastError() != hipSuccess) return TIDE_ERR_HIP;
+  }
+  if (need > filled) {
+    const uint32_t n16 = (uint32_t)((need - filled) / 16);
+    hipLaunchKernelGGL(zero_kernel, dim3((n16 + 255) / 256), dim3(256), 0, stream,
+                       reinterpret_cast<u32x4_t*>(ws + filled), n16);
+    if (hipGetLastError() != hipSuccess) return TIDE_ERR_HIP;
+  }
+  return TIDE_OK;
 }
 
 // Waits until every workgroup of the slot's last reader has set its flag.  Normally it
@@ -150,9 +194,13 @@ bool capturing(hipStream_t stream) {
 }
 
 // Stages the plan.  readers: the workgroups of the one kernel that reads it, if it may be read
-// in place (0: not).  Under debug checks the kernel needs the zeroed header, and in a captured
-// graph the copy that a replay runs again, so both keep the copy into the workspace.
+// in place (0: not).  Under debug checks the kernel needs the zeroed header, which keeps the
+// copy into the workspace; under capture no staging slot is used.
 int upload(const Plan& plan, void* workspace, hipStream_t stream, uint32_t readers, Staged* out) {
+  if (capturing(stream)) {
+    out->plan = static_cast<const uint8_t*>(workspace);
+    return put_plan(plan, workspace, stream);
+  }
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0) return TIDE_ERR_HIP;
   std::lock_guard<std::mutex> lock(g_mutex);
@@ -191,7 +239,7 @@ int upload(const Plan& plan, void* workspace, hipStream_t stream, uint32_t reade
     s.cap = cap;
   }
   s.seq = s.seq + 1 == 0 ? 1 : s.seq + 1;  // never 0, the flags' initial value
-  if (readers > 0 && readers <= kInPlaceGroups && !debug_checks() && !capturing(stream)) {
+  if (readers > 0 && readers <= kInPlaceGroups && !debug_checks()) {
     // (the flags a decode plan ends with need no zeros)
     memcpy(s.host, plan.blob.data(), plan.stream ? plan.tickets_off : need);
     s.nblocks = readers;
@@ -307,8 +355,8 @@ int run_extend(int op, const void* q, const void* k_pool, const void* v_pool, in
 
 // Shared path of tide_decode_attn, tide_decode_append_attn (fused: k_new / v_new) and
 // tide_decode_attn_noalloc (in_scratch: the call runs in the static device scratch, its
-// work list is copied there with hipMemcpyAsync from the plan's host buffer, and nothing
-// is allocated).
+// work list is copied there with hipMemcpyAsync from the plan's host buffer, or put there by
+// kernels under capture, and nothing is allocated).
 int run_decode(const void* q, const void* k_new, const void* v_new, const void* k_pool,
                const void* v_pool, int64_t num_pages, const int32_t* block_table,
                int32_t bt_stride, int32_t num_tasks, const int32_t* kv_lens,
@@ -331,10 +379,15 @@ int run_decode(const void* q, const void* k_new, const void* v_new, const void* 
     if (plan.total_bytes > (size_t)TIDE_NOALLOC_SCRATCH_BYTES) return TIDE_ERR_CAPACITY;
     rc = scratch_address(&workspace);
     if (rc != TIDE_OK) return rc;
-    // the blob starts with the zeroed header, so this also clears the error flags
-    if (hipMemcpyAsync(workspace, plan.blob.data(), plan.blob.size(), hipMemcpyHostToDevice, s) !=
-        hipSuccess)
+    // the blob starts with the zeroed header, so this also clears the error flags; a captured
+    // copy would read the plan's host buffer at every replay, long after it is freed
+    if (capturing(s)) {
+      rc = put_plan(plan, workspace, s);
+      if (rc != TIDE_OK) return rc;
+    } else if (hipMemcpyAsync(workspace, plan.blob.data(), plan.blob.size(), hipMemcpyHostToDevice,
+                              s) != hipSuccess) {
       return TIDE_ERR_HIP;
+    }
     st.plan = static_cast<const uint8_t*>(workspace);
   } else {
     if (!workspace) return TIDE_ERR_INVALID_ARG;

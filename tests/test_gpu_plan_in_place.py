@@ -1,8 +1,8 @@
 """Plans read in place in the staging ring, or copied into the workspace (needs an MI355X).
 
-A small call's kernel reads its work list where it was staged; debug checks and graph capture
-keep the copy.  Both must give the same bits, over more calls than the ring has slots, and a
-captured call must give them at every replay.
+A small call's kernel reads its work list where it was staged; debug checks keep the copy.
+Both must give the same bits, over more calls than the ring has slots.  Under graph capture the
+work list goes into the graph, and a captured call must give its bits at every replay.
 """
 import numpy as np
 import pytest
@@ -52,25 +52,41 @@ def test_in_place_equals_copied(case, monkeypatch):
 
 
 def test_captured_call_replays(case):
+    """Every replay gives the captured calls' bits, whatever was called in between: here more
+    calls than the ring has slots, of other lengths, before the first replay and after each."""
     wl, kv, q, qd, k, v = case
-    want = bits(kv.extend(q, wl.prefix_lens, wl.extend_lens), kv.decode(qd, wl.seq_lens))
+    hq, hkv, d = wl.spec.num_q_heads, wl.spec.num_kv_heads, wl.spec.head_dim
+    n = wl.num_tasks
+    owl = W.custom_workload(hq, hkv, d, [40 + 7 * i % 50 for i in range(n)], [2 + i % 3 for i in range(n)], seed=5)
+    odw = DeviceWorkload(owl)
+    odw.append_extend()
+    oq = dev_bf16(owl.packed("q", owl.extend_ranges()))
+    oqd = oq[:n].contiguous()
+
+    def others():
+        for _ in range(12):
+            odw.kv.extend(oq, owl.prefix_lens, owl.extend_lens)
+            odw.kv.decode(oqd, owl.seq_lens)
+        odw.kv.decode_noalloc(oqd, owl.seq_lens)
+
+    want = bits(kv.extend(q, wl.prefix_lens, wl.extend_lens), kv.decode(qd, wl.seq_lens),
+                kv.decode_noalloc(qd, wl.seq_lens, num_splits=2))
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     graph = torch.cuda.CUDAGraph()
-    e, d = torch.empty_like(q), torch.empty_like(qd)
-    with torch.cuda.stream(side):
-        kv.extend(q, wl.prefix_lens, wl.extend_lens, out=e)
-        kv.decode(qd, wl.seq_lens, out=d)
+    outs = e, d, dn = torch.empty_like(q), torch.empty_like(qd), torch.empty_like(qd)
     torch.cuda.synchronize()
     with torch.cuda.graph(graph, stream=side):
         kv.extend(q, wl.prefix_lens, wl.extend_lens, out=e)
         kv.decode(qd, wl.seq_lens, out=d)
+        kv.decode_noalloc(qd, wl.seq_lens, num_splits=2, out=dn)
     for _ in range(4):
-        e.zero_()
-        d.zero_()
+        others()
+        torch.cuda.synchronize()
+        for t in outs:
+            t.zero_()
         graph.replay()
         torch.cuda.synchronize()
-        for a, b in zip(bits(e, d), want):
+        for a, b in zip(bits(*outs), want):
             assert torch.equal(a, b)
-        kv.decode(qd, wl.seq_lens)  # eager work between the replays
-        torch.cuda.synchronize()
+        kv.decode(qd, wl.seq_lens)
