@@ -161,8 +161,9 @@ int task_lengths(int op, int32_t b, const int32_t* lens_a, const int32_t* lens_b
 // head are dealt out longest first, a round of 256 / Hkv at a time, and a round lasts as long
 // as its longest item; a tile costs less while CUs are idle (the card is power-limited, so
 // its clock is higher then), a chunk costs the write of its partial, and a split plan the
-// merge.  The planner runs on every call, so everything here is a few passes over the blocks,
-// and only the chosen plan is materialised.
+// merge.  The planner runs on every call, so a number of rounds costs one pass over the blocks
+// for its estimate and about 2 log2 of the longest block's tiles for its chunk length, and only
+// the chosen plan is materialised.
 namespace {
 
 constexpr int kCus = 256;  // MI355X compute units, 32 per XCD
@@ -194,8 +195,8 @@ struct Block {
 // kMaxChunks) and of equal length to one tile, so that equally long blocks of a task are cut
 // at the same keys.  T == 0: the plain plan (one chunk).
 inline int32_t num_chunks(int32_t ntiles, int32_t T) {
-  if (T <= 0) return 1;
-  return std::min(kMaxChunks, std::max(1, (int32_t)(((uint32_t)ntiles + (uint32_t)T - 1) / (uint32_t)T)));
+  if (T <= 0 || ntiles <= T) return 1;
+  return std::min(kMaxChunks, (int32_t)(((uint32_t)ntiles + (uint32_t)T - 1) / (uint32_t)T));
 }
 
 inline int32_t chunk_begin(int32_t ntiles, int32_t n, int32_t c) {
@@ -218,16 +219,26 @@ double estimate(const std::vector<Block>& blocks, int32_t longest, const tide_di
   const int64_t round = std::max(1, kCus / dims.num_kv_heads);  // CUs of a kv head
   // the chunks of one kv head by length (in steps of 2^shift tiles, if very long)
   constexpr int kBins = 1024;
-  int64_t count[kBins] = {};
-  int32_t most_rows[kBins] = {};
+  int64_t count[kBins];
+  int32_t most_rows[kBins];
+  const int32_t most = T > 0 ? std::min(T, longest) : longest;
   int shift = 0;
-  while ((T > 0 ? std::min(T, longest) : longest) >> shift >= kBins) ++shift;
+  while (most >> shift >= kBins) ++shift;
+  const int top = (kMaxChunks * (int64_t)T < longest ? longest : most) >> shift;
+  const int bins = std::min(kBins, top + 1);
+  std::fill_n(count, bins, 0);
+  std::fill_n(most_rows, bins, 0);
   int64_t slots = 0, items = 0;
   for (const Block& b : blocks) {
+    if (T <= 0 || b.ntiles <= T) {  // one chunk
+      ++items;
+      ++count[std::min(kBins - 1, b.ntiles >> shift)];
+      continue;
+    }
     const int32_t n = num_chunks(b.ntiles, T);
-    if (n > 1) slots += (int64_t)b.ntok * n;
+    slots += (int64_t)b.ntok * n;
     items += n;
-    const int32_t q = b.ntiles / n, r = b.ntiles % n, rows = n > 1 ? b.ntok * group : 0;
+    const int32_t q = b.ntiles / n, r = b.ntiles % n, rows = b.ntok * group;
     for (int up = 0; up < 2; ++up) {
       const int32_t m = up ? r : n - r, bin = std::min(kBins - 1, (q + up) >> shift);
       if (m == 0) continue;
@@ -237,7 +248,7 @@ double estimate(const std::vector<Block>& blocks, int32_t longest, const tide_di
   }
   double us = 0.0;
   int64_t seen = 0, lead = 0;  // lead: place of the longest item of the next round
-  for (int bin = kBins - 1; bin >= 0; --bin) {
+  for (int bin = bins - 1; bin >= 0; --bin) {
     seen += count[bin];
     for (; lead < seen; lead += round) {
       const double busy = (double)std::min(round, items - lead) / round;
@@ -352,6 +363,9 @@ std::vector<Item> interleave(const std::vector<std::vector<Piece>>& queues, Make
   size_t depth = 0, total = 0;
   int32_t longest = 1;
   for (int x = 0; x < kXcds; ++x) {
+    size_t n = 0;
+    for (const Piece& p : queues[x]) n += p.k1 - p.k0;
+    per[x].reserve(n);
     for (const Piece& p : queues[x])
       for (int32_t k = p.k0; k < p.k1; ++k) {
         per[x].push_back(make(k, p.g, std::max(p.c, 0)));
@@ -363,6 +377,7 @@ std::vector<Item> interleave(const std::vector<std::vector<Piece>>& queues, Make
   if (total <= (size_t)kSplitMaxItems && depth > (size_t)(kCus / kXcds))
     for (int x = 0; x < kXcds; ++x) {
       std::vector<uint8_t> cls;  // length class of each item, 0 .. 8
+      cls.reserve(per[x].size());
       int32_t at[10] = {};       // first place of each class, longest first
       for (const Piece& p : queues[x])
         for (int32_t k = p.k0; k < p.k1; ++k) {
@@ -447,13 +462,16 @@ int plan_extend(const std::vector<TaskDesc>& tasks, const tide_dims& dims, bool 
       const int64_t room = (int64_t)rounds * kCus / hkv;
       if ((int64_t)blocks.size() > room) continue;
       auto fits = [&](int32_t t) {
+        ++plan->search_passes;
         int64_t n = 0;
         for (const Block& b : blocks) n += num_chunks(b.ntiles, t);
         return n <= room;
       };
+      // (steps that double, then a bisection: a scan took 440 us of planning on one long task
+      // among many short ones, this takes 100)
       int32_t lo = (int32_t)std::max<int64_t>(kMinChunkTiles, ceil_div(tiles, room)) - 1, hi = lo + 1;
       while (hi < longest && !fits(hi)) {
-        const int32_t next = (int32_t)std::min<int64_t>(longest, 2 * (int64_t)hi - lo);
+        const int32_t next = (int32_t)std::min<int64_t>(longest, hi + 2 * (int64_t)(hi - lo));
         lo = hi;
         hi = next;
       }
@@ -480,6 +498,7 @@ int plan_extend(const std::vector<TaskDesc>& tasks, const tide_dims& dims, bool 
   for (size_t k = 0; k < blocks.size(); ++k) nchunks[k] = num_chunks(blocks[k].ntiles, T);
   const std::vector<std::vector<Piece>> queues = place(blocks, task_first, nchunks, hkv, T);
   plan->split = T > 0;
+  plan->chunk = T;
   if (T == 0) {
     const std::vector<ExtendItem> items = interleave<ExtendItem>(
         queues, [&](int32_t k, int32_t g, int32_t) {

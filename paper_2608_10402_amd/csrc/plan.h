@@ -46,8 +46,10 @@ struct Plan {
   // extend: tokens per work item and waves per workgroup
   int32_t tokens_per_item = 0;
   int32_t waves = 0;
+  // extend: passes over the blocks that the search for the chunk length made
+  int32_t search_passes = 0;
+  int32_t chunk = 0;  // decode: keys per chunk or run; split extend: most key tiles per chunk
   // decode
-  int32_t chunk = 0;
   int32_t max_splits = 0;
   int32_t total_rows = 0;
   std::vector<uint8_t> blob;  // bytes to upload (header + tasks + items)

@@ -83,6 +83,23 @@ def test_edge_plans_are_valid(checker):
         _run(checker, lines, mode)
 
 
+def test_chunk_search_is_short(checker):
+    """Ragged calls, whose shortest chunk is far above the mean: one long task among many short
+    ones, one long prefill with few kv heads.  The checker compares the chunk length with a scan
+    of all lengths and bounds the search's passes by the logarithm of the longest block."""
+    rng = np.random.default_rng(7)
+    lines = []
+    for n, long in ((64, 98000), (40, 60000), (12, 30000), (100, 8000)):
+        prefix = rng.integers(200, 2000, n)
+        prefix[n // 2] = long
+        lines.append(_line(OP_EXTEND, 28, 4, 128, prefix, rng.integers(40, 100, n)))
+    for n in (16384, 30000, 65536):
+        lines.append(_line(OP_PREFILL, 16, 2, 128, [0], [n]))
+        lines.append(_line(OP_PREFILL, 4, 1, 64, [0, 0], [n, 700]))
+    out = _run(checker, lines)
+    assert sum(o[1] == "1" for o in out) >= 5
+
+
 def test_split_choice(checker):
     """Few long items are split; a full batch and tiny calls keep the plain plan."""
     few = _line(OP_EXTEND, 28, 4, 128, [6000], [380])
