@@ -120,14 +120,17 @@ TIDE_HD inline int32_t stream_groups(int32_t runs, int32_t num_kv_heads) {
 // combined per workgroup, into one slot for each (workgroup, task); a part that ends inside
 // its run has a slot of its own, at most one for a task and one for a run.  Along the runs
 // either the workgroup or the task grows from one such part to the next, so their sum is a
-// slot index; where tasks outnumber runs, the (first) run is a smaller one.
+// slot index; where tasks outnumber runs, the (first) run is a smaller one.  A single run cuts
+// no task, and with the over 1,024 kv heads that lead to one its slots would be large.
 struct StreamSlots {
   int32_t runs, tasks, per;  // per: runs of a workgroup
   TIDE_HD int32_t groups() const { return (runs + per - 1) / per; }
   TIDE_HD int32_t open_slots() const {
     return (int64_t)groups() + tasks < runs ? groups() + tasks : runs;
   }
-  TIDE_HD int32_t count() const { return open_slots() + (tasks < runs ? tasks : runs); }
+  TIDE_HD int32_t count() const {
+    return runs == 1 ? 0 : open_slots() + (tasks < runs ? tasks : runs);
+  }
   TIDE_HD int32_t open(int32_t run, int32_t task) const {
     return (int64_t)groups() + tasks < runs ? run / per + task : run;
   }

@@ -40,6 +40,17 @@ def test_runs_cover_the_call(tmp_path):
     assert r.returncode == 0 and len(out) == len(lines) and all(o.startswith("ok") for o in out), r.stdout[-500:]
 
 
+@pytest.mark.parametrize("heads, kv", [((65536, 4096, 128), [28]), ((114452, 8804, 128), [900]),
+                                       ((214592, 53648, 64), [21]), ((30720, 1920, 128), [2000] * 3)])
+def test_one_run_needs_no_partials(heads, kv):
+    """Over 1,024 kv heads make one run of the whole call, which cuts no task: the call needs the
+    plan's bytes and fits the static scratch of tide_decode_attn_noalloc at any head count."""
+    import paper_2608_10402_amd as tide
+    dims = tide.make_dims(*heads, 0.1)
+    size = tide.tide_workspace_size(tide.TIDE_OP_DECODE, np.array(kv, np.int32), None, dims)
+    assert size <= 2048
+
+
 def test_no_scratch_access_inside_loops(tmp_path):
     """A spill reload inside the step loop would wait for every K/V load in flight."""
     from test_codegen import _asm, loops_with_scratch
@@ -49,6 +60,7 @@ def test_no_scratch_access_inside_loops(tmp_path):
 
 GPU_CASES = {
     "one_key": (16, 1, 64, [1]),
+    "one_run_many_heads": (1100, 1100, 64, [5, 40, 16]),
     "page_and_step_ends": (28, 4, 128, [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65]),
     "several_units_a_run": (8, 8, 128, [17 + 5 * (i % 9) for i in range(400)]),
     "units_end_with_runs": (8, 8, 128, [64 * 32] * 16),   # 8192 steps: 4 a wave, 16 waves a unit
