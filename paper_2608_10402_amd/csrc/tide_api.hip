@@ -176,6 +176,9 @@ struct Staged {
   const uint8_t* plan = nullptr;  // the workspace, or a staging slot
   PlanReads reads = {nullptr, 0};
   StagingSlot* slot = nullptr;    // set with reads.done
+  // the ring's, held with a slot until its reader is launched: until then another call that
+  // came round to the slot would wait for flags that no kernel is there to set
+  std::unique_lock<std::mutex> lock;
 };
 
 // A plan that at most this many workgroups read, once each, is read where it was staged: a
@@ -203,7 +206,7 @@ int upload(const Plan& plan, void* workspace, hipStream_t stream, uint32_t reade
   }
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0) return TIDE_ERR_HIP;
-  std::lock_guard<std::mutex> lock(g_mutex);
+  std::unique_lock<std::mutex> lock(g_mutex);
   if ((int)g_staging.size() <= dev) g_staging.resize(dev + 1, nullptr);
   if (!g_staging[dev]) g_staging[dev] = new DeviceStaging();
   DeviceStaging& ds = *g_staging[dev];
@@ -247,6 +250,7 @@ int upload(const Plan& plan, void* workspace, hipStream_t stream, uint32_t reade
     out->plan = static_cast<const uint8_t*>(s.dev);
     out->reads = PlanReads{s.flags_dev, s.seq};
     out->slot = &s;
+    out->lock = std::move(lock);
     return TIDE_OK;
   }
   memcpy(s.host, plan.blob.data(), need);
@@ -262,14 +266,10 @@ int upload(const Plan& plan, void* workspace, hipStream_t stream, uint32_t reade
   return TIDE_OK;
 }
 
-int finish(hipError_t launch_status, const Staged& st, void* workspace, hipStream_t stream) {
-  if (launch_status != hipSuccess) {
-    if (st.slot) {  // nothing will read the slot
-      std::lock_guard<std::mutex> lock(g_mutex);
-      if (st.slot->seq == st.reads.seq) st.slot->pending = false;
-    }
-    return TIDE_ERR_HIP;
-  }
+int finish(hipError_t launch_status, Staged& st, void* workspace, hipStream_t stream) {
+  if (st.slot && launch_status != hipSuccess) st.slot->pending = false;  // nothing will read it
+  if (st.lock.owns_lock()) st.lock.unlock();
+  if (launch_status != hipSuccess) return TIDE_ERR_HIP;
   if (!debug_checks()) return TIDE_OK;
   if (hipStreamSynchronize(stream) != hipSuccess) return TIDE_ERR_HIP;
   int32_t flags = 0;
