@@ -171,8 +171,8 @@ def counter_traffic(workload: str, kernel: str):
 def kernel_label(wl, stage: str) -> str:
     """The instantiation the stage's dominant kernel runs as, from the plan the library
     makes for these lengths (tide_plan_info_get): extend<D, lse, split, append>,
-    decode_stream<D, append, waves> or decode_split<D, shared, append, waves> (waves per
-    workgroup; the stream kernel up to 208 32-key steps a run, 2048 / Hkv runs a kv head)."""
+    decode_stream<D, append, waves> for a decode that goes by runs, else
+    decode_split<D, shared, append, waves> (waves per workgroup)."""
     import paper_2608_10402_amd as tide
     s = wl.spec
     dims = tide.make_dims(s.num_q_heads, s.num_kv_heads, s.head_dim, wl.sm_scale)
@@ -183,8 +183,7 @@ def kernel_label(wl, stage: str) -> str:
     if stage == "decode":
         kv = wl.seq_lens + (1 if s.decode_steps else 0)  # the first of the fused decode steps
         info = tide.tide_plan_info_get(tide.TIDE_OP_DECODE, kv, None, dims)
-        steps = int(np.sum(-(-np.asarray(kv, dtype=np.int64) // 32)))
-        if -(-steps // max(1, 2048 // s.num_kv_heads)) <= 208:
+        if info["run_steps"]:
             return "decode_stream_kernel<%d, %s, %d>" % (
                 d, "true" if s.decode_steps else "false", info["waves_per_group"])
         return "decode_split_kernel<%d, false, %s, %d>%s" % (

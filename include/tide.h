@@ -143,7 +143,7 @@ typedef struct tide_plan_info {
   int32_t split;            /* extend/prefill: 1 when split-KV chunks and a merge run */
   int32_t max_splits;       /* decode: the most splits of any task */
   int32_t merge_in_kernel;  /* decode: 1 when the split kernel merges (no merge kernel) */
-  int32_t reserved;
+  int32_t run_steps;        /* decode: 32-key steps per run; 0 when the call goes by chunks */
   size_t workspace_bytes;
 } tide_plan_info;
 TIDE_API int tide_plan_info_get(int op, int32_t num_tasks, const int32_t* lens_a,

@@ -52,7 +52,7 @@ class tide_dims(ctypes.Structure):
 class tide_plan_info(ctypes.Structure):
     _fields_ = [("num_items", ctypes.c_int32), ("waves_per_group", ctypes.c_int32),
                 ("split", ctypes.c_int32), ("max_splits", ctypes.c_int32),
-                ("merge_in_kernel", ctypes.c_int32), ("reserved", ctypes.c_int32),
+                ("merge_in_kernel", ctypes.c_int32), ("run_steps", ctypes.c_int32),
                 ("workspace_bytes", ctypes.c_size_t)]
 
 
@@ -258,7 +258,7 @@ def tide_plan_info_get(op: int, lens_a, lens_b, dims: tide_dims, num_splits: int
     info = tide_plan_info()
     _check(load().tide_plan_info_get(op, n, a_p, b_p, ctypes.byref(dims), int(num_splits),
                                      ctypes.byref(info)), "tide_plan_info_get")
-    return {name: getattr(info, name) for name, _ in tide_plan_info._fields_ if name != "reserved"}
+    return {name: getattr(info, name) for name, _ in tide_plan_info._fields_}
 
 
 def alloc_workspace(nbytes: int, device="cuda") -> torch.Tensor:

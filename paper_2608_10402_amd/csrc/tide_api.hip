@@ -504,6 +504,7 @@ TIDE_API int tide_plan_info_get(int op, int32_t num_tasks, const int32_t* lens_a
           plan.stream ? stream_waves(plan.num_items) : decode_waves(plan.num_items);
       out->max_splits = plan.max_splits;
       out->merge_in_kernel = plan.fold_merge ? 1 : 0;
+      out->run_steps = plan.steps;
     } else if (op == TIDE_OP_KV_APPEND) {
       out->waves_per_group = append_waves();
     } else {

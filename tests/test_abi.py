@@ -340,6 +340,11 @@ def test_plan_info_matches_workspace_size_and_launch_rules():
     many = tide.tide_plan_info_get(tide.TIDE_OP_DECODE, np.asarray([9000] * 4, np.int32), None,
                                    dims, num_splits=40)
     assert one["max_splits"] == 1 and one["merge_in_kernel"] == 1
+    assert one["run_steps"] == many["run_steps"] == 0  # chunks, when a split count is asked for
+    # 256 runs per kv head: 256 * 157 steps make runs of 157, 256 * 313 would make runs of 313
+    for keys, steps in ((5000, 157), (10000, 0)):
+        info = tide.tide_plan_info_get(tide.TIDE_OP_DECODE, np.asarray([keys] * 256, np.int32), None, dims)
+        assert info["run_steps"] == steps
     # 40 splits asked: chunks of ceil(9000 / 40) keys rounded up to 32 -> 256 -> 36 splits
     assert many["max_splits"] == 36 and many["merge_in_kernel"] == 0
     p, e = np.asarray([1000, 20], np.int32), np.asarray([300, 5], np.int32)
