@@ -17,6 +17,13 @@ from gpu_harness import assert_close, assert_lse, host_f64, log
 pytestmark = pytest.mark.gpu
 
 
+def check_plan(kv, p, e, split):
+    """TIDE_EXTEND_SPLIT cuts a call only where a block spans enough tiles: that it did."""
+    info = tide.tide_plan_info_get(tide.TIDE_OP_EXTEND, np.array([p], np.int32),
+                                   np.array([e], np.int32), kv.dims)
+    assert info["split"] == int(split)
+
+
 def build(hq, hkv, d, prefix, extend, scaled, seed, bad=None):
     """One task; keys `scaled` = {position: factor}; `bad` = (position, value) sets a key."""
     g = torch.Generator().manual_seed(seed)
@@ -45,9 +52,9 @@ def build(hq, hkv, d, prefix, extend, scaled, seed, bad=None):
 CASES = {
     "unmasked_jump": (4, 1, 128, 300, 40, {130: 64.0}),
     "two_jumps": (8, 2, 64, 500, 70, {70: 40.0, 333: 300.0}),
-    "diagonal_jump": (7, 1, 128, 128, 100, {150: 200.0}),
+    "diagonal_jump": (7, 1, 128, 320, 100, {350: 200.0}),
     "first_tile_largest": (4, 2, 128, 260, 33, {5: 300.0}),
-    "last_key": (2, 2, 64, 255, 1, {255: 500.0}),
+    "last_key": (2, 2, 64, 447, 1, {447: 500.0}),
     "long_split": (4, 2, 128, 2600, 50, {40: 30.0, 1000: 100.0, 2610: 400.0}),
 }
 
@@ -59,6 +66,7 @@ def test_score_jumps(name, split, monkeypatch):
     hq, hkv, d, p, e, scaled = CASES[name]
     log("jump case %s split %s" % (name, split))
     kv, q, kn, vn, ref, ref_lse = build(hq, hkv, d, p, e, scaled, seed=len(name))
+    check_plan(kv, p, e, split)
     lse = torch.empty((e, hq), dtype=torch.float32, device="cuda")
     fused = kv.extend_append(q, kn, vn, [p], [e], lse=lse)
     assert_close(fused, ref, "%s fused" % name)
@@ -78,6 +86,7 @@ def test_large_values_stay_finite(d, split, monkeypatch):
     p, e = 400, 60
     log("large values d %d split %s" % (d, split))
     kv, q, kn, vn, ref, _ = build(8, 2, d, p, e, {150: 12.0, 333: 16.0}, seed=d)
+    check_plan(kv, p, e, split)
     kv.v_pool.mul_(2.0 ** 106)
     out = kv.extend_append(q, kn, vn * 2.0 ** 106, [p], [e])
     assert_close(out.double() * 2.0 ** -106, ref, "large values")

@@ -37,8 +37,21 @@ def bits(*ts):
     return [t.view(torch.int16).clone() for t in ts]
 
 
+def in_place(kv, call):
+    """call()'s result, and whether it left the workspace's header alone: a copied plan begins
+    with zeros there, and a plan read in the staging slot does not touch it."""
+    head = kv._ws[:256]
+    head.fill_(0x5A)
+    got = call()
+    torch.cuda.synchronize()
+    kept = bool((head == 0x5A).all())
+    assert kept or not head.any()
+    return got, kept
+
+
 def test_in_place_equals_copied(case, monkeypatch):
     wl, kv, q, qd, k, v = case
+    monkeypatch.setenv("TIDE_EXTEND_SPLIT", "0")  # a split plan is always copied
     got = []
     for checks in ("0", "1"):
         monkeypatch.setenv("TIDE_DEBUG_CHECKS", checks)
@@ -47,8 +60,39 @@ def test_in_place_equals_copied(case, monkeypatch):
             e = kv.extend(q, wl.prefix_lens, wl.extend_lens)
             d = kv.decode(qd, wl.seq_lens)
         got.append(bits(e, d, kv.k_pool, kv.v_pool))
+        for call in (lambda: kv.append(k, v, wl.prefix_lens, wl.extend_lens),
+                     lambda: kv.extend(q, wl.prefix_lens, wl.extend_lens),
+                     lambda: kv.decode(qd, wl.seq_lens)):
+            assert in_place(kv, call)[1] == (checks == "0")
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("op, tasks, want", [
+    ("append", 512, True), ("append", 513, False),   # one workgroup a page of 4 kv heads
+    ("extend", 128, True), ("extend", 129, False),   # one a task and kv head
+    ("decode", 512, True), ("decode", 513, False),   # 512 runs of a step; 257 of two steps
+])
+def test_where_plans_are_read_in_place(op, tasks, want, monkeypatch):
+    """The largest calls whose plan at most 512 workgroups read once each, and the next."""
+    wl = W.custom_workload(8, 4, 64, [3 + i % 9 for i in range(tasks)], [2] * tasks, seed=tasks)
+    kv = DeviceWorkload(wl).kv
+    q, k, v = (dev_bf16(wl.packed(x, wl.extend_ranges())) for x in "qkv")
+    kv.append(k, v, wl.prefix_lens, wl.extend_lens)
+    qd = q[1::2].contiguous()
+    call = {"append": lambda: kv.append(k, v, wl.prefix_lens, wl.extend_lens),
+            "extend": lambda: kv.extend(q, wl.prefix_lens, wl.extend_lens),
+            "decode": lambda: kv.decode(qd, wl.seq_lens)}[op]
+    monkeypatch.setenv("TIDE_DEBUG_CHECKS", "0")
+    call()  # its workspace is large enough from here on
+    out, kept = in_place(kv, call)
+    assert kept == want
+    pools = bits(kv.k_pool, kv.v_pool)
+    monkeypatch.setenv("TIDE_DEBUG_CHECKS", "1")
+    other, kept = in_place(kv, call)
+    assert not kept
+    assert all(torch.equal(a, b) for a, b in zip(pools, bits(kv.k_pool, kv.v_pool)))
+    assert out is None or torch.equal(*bits(out, other))
 
 
 def test_captured_call_replays(case):
