@@ -38,8 +38,8 @@
 //     lanes of an operand read hit distinct banks.
 //   * Scores stay raw until one FMA applies sm_scale*log2(e) and subtracts the running
 //     max before v_exp_f32.  A row's reference is the maximum of its first tile and is only
-//     raised when a tile's weights outgrow it (kTileSumMax), so later tiles need no
-//     maximum and the O rescale is skipped on most of them.
+//     raised when a tile exceeds it by more than kRescaleSlack, which a tile's weights show
+//     afterwards (kTileSumMax): most tiles need no maximum and no O rescale.
 //   * Causal masking is applied only on tiles that cross the diagonal.  On the last
 //     tile, V operands of key slots at or beyond the task's length are zeroed in
 //     registers, so NaN/Inf garbage in unused pool slots can never reach the output.
@@ -88,14 +88,16 @@ __device__ __forceinline__ void dma16_lane(const void* src, uint8_t* lds) {
   __builtin_amdgcn_global_load_lds((glb_void*)src, (lds_void*)lds, 16, 0, 0);
 }
 
-// A tile's weights are kept as evaluated against the row's reference while a lane's share of
-// their sum (32 keys) is below this, so no weight reaches 2^kRescaleSlack and every tile whose
-// maximum exceeds the reference by more than that raises it.  The largest weight of a row is
-// rounded to bf16 unless its key is the reference (2^0 = 1 is exact), and larger weights leave
-// V less of fp32's range, so the bound is no higher than decode's: with 2^30 here, 16 tasks of
-// 4k-24k keys, a tenth of them scaled by 4, were 14% further from the exact result before the
-// output's own rounding (rms 9.1e-4 against 8.4e-4 with 2^8 or with a maximum per tile).
+// A tile evaluated without its maximum stays as it is while each lane's share of its weights' sum
+// (32 keys) is below this, so that no weight reaches 2^kRescaleSlack: a row's reference is raised
+// by the same rule as with a maximum per tile.  The rule matters: the largest weight of a row is
+// rounded to bf16 unless its key is the reference (2^0 = 1 is exact), and larger weights leave V
+// less of fp32's range.  Rows over 12,800 keys, a tenth of them scaled by 4: rms error before the
+// output's own rounding 8.4e-4, and 9.1e-4 with 2^30 here.
 constexpr float kTileSumMax = 256.0f;  // 2^kRescaleSlack
+// A wave that had to evaluate a tile again takes maxima first until this many tiles went by without
+// a raised reference (16 to 256 measured the same).
+constexpr int kHotTiles = 64;
 
 // Physical position of 16-byte granule g of K tile row r.
 template <int D>
@@ -439,7 +441,7 @@ void extend_attn_kernel(ExtendArgs a) {
   for (int t = 0; t < kDT; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[t][e] = 0.0f;
-  float m_ref = kNoMax, negm = -kNoMax, l_part = 0.0f, l_exact = 0.0f;
+  float m_ref = kNoMax, l_part = 0.0f, l_exact = 0.0f;
   f32x16 sa[2], sb[2];  // S of two consecutive tiles (the one in softmax, the next one)
   u32x4 pa[4], pb[4];   // bf16 probabilities of two consecutive tiles, 16-key chunks
 
@@ -482,40 +484,47 @@ void extend_attn_kernel(ExtendArgs a) {
 
   constexpr int kAhead = 3;  // operand reads in flight ahead of the MFMAs
 
-  // Raises the reference of the rows whose tile sum is not below kTileSumMax to the tile's
-  // maximum, rescales what they accumulated and evaluates the tile again.  Rows below it
-  // keep their reference (and get the same weights and sums again), so a row's result does
-  // not depend on the other rows of the wave.  Lanes l and l^32 hold one row: either's sum
-  // counts.
-  auto redo = [&](const f32x16(&s)[2], u32x4(&p)[4], float& lt, float& le)
-      __attribute__((always_inline)) {
-    float t0, t1;
-    lane_pair(lt, t0, t1);
-    const bool over = !(t0 < kTileSumMax) || !(t1 < kTileSumMax);
-    float mc[4], x0, x1;  // four chains, as in the first tile
+  // Tiles for which this wave goes on taking each tile's maximum first (see `block`).
+  int hot = 0;
+
+  // The maximum of a tile's scores in each row (lanes l and l^32 hold one row), scaled.
+  auto row_max = [&](const f32x16(&s)[2]) __attribute__((always_inline)) -> float {
+    float mc[4], x0, x1;  // four chains, as in `block`
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       auto e = [&](int f) { return s[c >> 1][8 * (c & 1) + f]; };
       mc[c] = max3(max3(max3(e(0), e(1), e(2)), e(3), e(4)), e(5), max3(e(6), e(7), e(7)));
     }
-    float mt = max3(max3(mc[0], mc[1], mc[2]), mc[3], mc[3]);
+    const float mt = max3(max3(mc[0], mc[1], mc[2]), mc[3], mc[3]);
     lane_pair(mt, x0, x1);
-    mt = max3(x0, x1, x1) * csc;
-    const float m_new = over && mt > m_ref ? mt : m_ref;
-    const float alpha = fast_exp2(m_ref - m_new);
-    m_ref = m_new;
-    negm = -m_new;
+    return max3(x0, x1, x1) * csc;
+  };
+  auto rescale = [&](float alpha) __attribute__((always_inline)) {
     l_part *= alpha;
     l_exact *= alpha;
 #pragma unroll
     for (int t = 0; t < kDT; ++t)
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[t][e] *= alpha;
+  };
+
+  // A tile some row of which has a sum not below kTileSumMax.  Rows that exceed their
+  // reference by more than the slack take the tile's maximum as their reference, what they
+  // accumulated is rescaled, and the tile is evaluated again; the others keep theirs (and get
+  // the same weights and sums again), so a row's result does not depend on the other rows of
+  // the wave.
+  auto redo = [&](const f32x16(&s)[2], u32x4(&p)[4], float& lt, float& le)
+      __attribute__((always_inline)) {
+    hot = kHotTiles;
+    const float mt = row_max(s);
+    const float m_new = mt > m_ref + kRescaleSlack ? mt : m_ref;
+    rescale(fast_exp2(m_ref - m_new));
+    m_ref = m_new;
     float lw[2] = {0.0f, 0.0f}, lx[2] = {0.0f, 0.0f};
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const float p0 = fast_exp2(fmaf(s[i >> 3][2 * (i & 7)], csc, negm));
-      const float p1 = fast_exp2(fmaf(s[i >> 3][2 * (i & 7) + 1], csc, negm));
+      const float p0 = fast_exp2(fmaf(s[i >> 3][2 * (i & 7)], csc, -m_ref));
+      const float p1 = fast_exp2(fmaf(s[i >> 3][2 * (i & 7) + 1], csc, -m_ref));
       const uint32_t w = pack_bf16x2(p0, p1);
       p[i / 4][i % 4] = w;
       lw[i % 2] = add_bf16x2(w, lw[i % 2]);
@@ -537,36 +546,40 @@ void extend_attn_kernel(ExtendArgs a) {
   // so the instructions issue in this order and every MFMA's 32 cycles hide about three
   // vector instructions.
   //
-  // Only the first tile (no P.V) takes its maximum before its exponentials.  Every later
-  // tile evaluates them against the reference the row already has and is checked
-  // afterwards, by its row sum: below kTileSumMax no key outgrew the reference by more than
-  // the slack that decode allows too.  A row whose sum is not below it (or is NaN) has its
-  // reference raised to the tile's maximum and the tile evaluated again (`redo`).  That
-  // takes 19 v_max3, the lane exchange, the reference update and its exponential out of
-  // every tile's 129 vector instructions, the maximum out of the chain from S to P, and
-  // every spill out of the plain kernel (it held 45-50 spilled VGPRs).  The kernel is bound
-  // by vector issue and by the card's power limit (the same launch over zeros runs 1.3x
-  // faster), so fewer instructions help twice: 64 tasks of 2k-16k keys and 64-2,048 new
-  // tokens (28 / 4 heads, d = 128) 4.06 -> 3.88 ms, 16 re-prefills of 2k-16k 9.98 -> 9.37 ms.
-  // Where scores grow along the context the second evaluations take the gain back: with a
-  // tenth of the keys scaled by 4, one of a workgroup's 8 waves raises a reference on about
-  // half of the tiles, and 16 image-sized extends with the log-sum-exp went 6.82 -> 6.94 ms.
+  // With kMax the tile's maximum comes first and raises the references it exceeds by more than
+  // the slack, as in the first tile.  Without, the tile is evaluated against the references the
+  // rows already have and checked afterwards, by its row sums: below kTileSumMax nothing
+  // exceeded them by more than the slack; otherwise (or with NaN) `redo`.  That takes 19
+  // v_max3, the lane exchange, the reference update and its exponential out of a tile's 129
+  // vector instructions, the maximum out of the chain from S to P, and every spill out of the
+  // plain kernel (it held 45-50 spilled VGPRs).  The kernel is bound by vector issue and by
+  // the card's power limit (the same launch over zeros runs 1.3x faster), so fewer
+  // instructions help twice: 64 tasks of 2k-16k keys and 64-2,048 new tokens (28 / 4 heads, d
+  // = 128) 4.00 -> 3.81 ms, 16 re-prefills of 2k-16k 9.82 -> 9.30 ms.
+  //
+  // Where scores have outliers a row's reference is raised about once in its first hundred
+  // tiles, some row's of a workgroup in every second tile, and evaluating those twice costs
+  // more than the maxima: 4 tasks of 0.5k-2k + 400 tokens (32 / 8), a tenth of the keys scaled
+  // by 4, 76.8 us with a maximum per tile, 88 without.  So a wave that evaluated a tile again
+  // goes on with maxima for a while (`walk`): 76.7 us, and 16 image-sized extends with the
+  // log-sum-exp 6.54 ms as with a maximum per tile (6.65 without).
   //
   // The operand reads of the next step's first kAhead MFMAs (P.V of this step's tile,
   // from vb_next) are issued in this step's last slots, into pre_next, before the barrier
   // that ends the step: the tiles they read were published one barrier earlier.  With
   // kPV the first kAhead operands of this step come from pre, read by the step before.
-  auto block = [&](auto pv_tag, auto diag_tag, int kt, f32x16(&s)[2], u32x4(&pcur)[4],
+  auto block = [&](auto pv_tag, auto max_tag, auto diag_tag, int kt, f32x16(&s)[2], u32x4(&pcur)[4],
                    const u32x4(&pprev)[4], const uint8_t* vb, const uint8_t* kb,
                    f32x16(&sn)[2], const u32x4(&pre)[kAhead], const uint8_t* vb_next,
                    u32x4(&pre_next)[kAhead]) __attribute__((always_inline)) {
     constexpr bool kPV = decltype(pv_tag)::value;
+    constexpr bool kMax = decltype(max_tag)::value;
     constexpr bool kDiag = decltype(diag_tag)::value;
     constexpr int nS = 2 * kDC, nPV = 4 * kDT;
     constexpr int nm = kPV ? nS + nPV : nS;
     constexpr int nMask = kDiag ? 32 : 0;
     constexpr int kPerGroup = kLse ? 14 : 12;  // vector ops per 4 probabilities
-    constexpr int kHead = kPV ? 0 : 22;        // first tile: max, exchange, reference
+    constexpr int kHead = kMax ? 23 : 0;       // max, exchange, reference update
     constexpr int nOps = nMask + kHead + 8 * kPerGroup + 1;
     const int kbase = kt * 64 + 8 * h;
     const f32x16 zero16 = {};
@@ -610,7 +623,7 @@ void extend_attn_kernel(ExtendArgs a) {
     };
 
     // softmax state
-    float mc[4], mt = 0.0f;
+    float mc[4], mt = 0.0f, m_new = 0.0f, alpha = 1.0f;
     float x[32], pr[32];
     uint32_t w[16];
     float lt[2], le[2];  // row sums of the tile, in two chains
@@ -641,14 +654,16 @@ void extend_attn_kernel(ExtendArgs a) {
         } else if constexpr (r == 19) {
           mt *= csc;
         } else if constexpr (r == 20) {
-          m_ref = mt > kNoMax ? mt : kNoMax;
+          m_new = mt > m_ref + kRescaleSlack ? mt : m_ref;
+        } else if constexpr (r == 21) {
+          if constexpr (kPV) alpha = fast_exp2(m_ref - m_new);
         } else {
-          negm = -m_ref;
+          m_ref = m_new;
         }
       } else if constexpr (k - nMask < kHead + 8 * kPerGroup) {
         constexpr int kk = k - nMask - kHead, g = kk / kPerGroup, r = kk % kPerGroup;
         if constexpr (r < 4) {
-          x[4 * g + r] = fmaf(E(4 * g + r), csc, negm);
+          x[4 * g + r] = fmaf(E(4 * g + r), csc, -m_ref);
         } else if constexpr (r < 8) {
           pr[4 * g + r - 4] = fast_exp2(x[4 * g + r - 4]);
         } else {
@@ -691,7 +706,13 @@ void extend_attn_kernel(ExtendArgs a) {
       static_for_range<lo, hi>([&](auto k) { op(k); });
       __builtin_amdgcn_sched_barrier(0);
     });
-    if constexpr (kPV) {
+    if constexpr (kPV && kMax) {
+      --hot;
+      if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+        rescale(alpha);
+        hot = kHotTiles;
+      }
+    } else if constexpr (kPV) {
       if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(lt[0] < kTileSumMax)) != 0, 0))
         redo(s, pcur, lt[0], le[0]);
     }
@@ -732,10 +753,10 @@ void extend_attn_kernel(ExtendArgs a) {
   // ---- iteration 0: softmax(0) with S(1) ---------------------------------------------
   u32x4 pre_a[kAhead], pre_b[kAhead];  // first operands of odd / even iterations
   if (tbase >= n_full)
-    block(std::false_type(), std::true_type(), tbase, sa, pa, pb, v_lds0, k_lds1, sb, pre_b,
+    block(std::false_type(), std::true_type(), std::true_type(), tbase, sa, pa, pb, v_lds0, k_lds1, sb, pre_b,
           v_lds0, pre_a);
   else
-    block(std::false_type(), std::false_type(), tbase, sa, pa, pb, v_lds0, k_lds1, sb, pre_b,
+    block(std::false_type(), std::true_type(), std::false_type(), tbase, sa, pa, pb, v_lds0, k_lds1, sb, pre_b,
           v_lds0, pre_a);
   wait_vmem<S::kGroup + S::kDma>();  // V(1) and K(2) landed
   tile_barrier();
@@ -746,26 +767,26 @@ void extend_attn_kernel(ExtendArgs a) {
   // (i+3) mod 4 (its first operands were read by iteration i-1), the reads ahead for
   // iteration i+1 take V slot i mod 4, and after the barrier the slots just read receive
   // K(i+5) and V(i+3).  The S, P and read-ahead buffers alternate with the parity of i.
-  auto step = [&](auto diag_tag, auto fuse_tag, int i, uint8_t* kb, uint8_t* vb,
+  auto step = [&](auto max_tag, auto diag_tag, auto fuse_tag, int i, uint8_t* kb, uint8_t* vb,
                   const uint8_t* vb_next, f32x16(&s)[2], f32x16(&sn)[2],
                   const u32x4(&pprev)[4], u32x4(&pcur)[4], const u32x4(&pre)[kAhead],
                   u32x4(&pre_next)[kAhead]) __attribute__((always_inline)) {
-    block(std::true_type(), diag_tag, tbase + i, s, pcur, pprev, vb, kb, sn, pre, vb_next, pre_next);
+    block(std::true_type(), max_tag, diag_tag, tbase + i, s, pcur, pprev, vb, kb, sn, pre, vb_next, pre_next);
     // the page ids of the next loads, fetched now so that the barrier hides their latency
     const PageRef kpg = page_ref(i + 5), vpg = page_ref(i + 3);
     wait_vmem<S::kGroup + S::kDma>();  // V(i+1) and K(i+2) landed
     tile_barrier();
     stream_pages(kb, vb, i + 5, i + 3, kpg, vpg, fuse_tag);
   };
-  auto four = [&](auto diag_tag, auto fuse_tag, int i) __attribute__((always_inline)) {
-    step(diag_tag, fuse_tag, i, k_lds2, v_lds0, v_lds1, sb, sa, pa, pb, pre_a, pre_b);
-    step(diag_tag, fuse_tag, i + 1, k_lds3, v_lds1, v_lds2, sa, sb, pb, pa, pre_b, pre_a);
-    step(diag_tag, fuse_tag, i + 2, k_lds0, v_lds2, v_lds3, sb, sa, pa, pb, pre_a, pre_b);
-    step(diag_tag, fuse_tag, i + 3, k_lds1, v_lds3, v_lds0, sa, sb, pb, pa, pre_b, pre_a);
+  auto four = [&](auto max_tag, auto diag_tag, auto fuse_tag, int i) __attribute__((always_inline)) {
+    step(max_tag, diag_tag, fuse_tag, i, k_lds2, v_lds0, v_lds1, sb, sa, pa, pb, pre_a, pre_b);
+    step(max_tag, diag_tag, fuse_tag, i + 1, k_lds3, v_lds1, v_lds2, sa, sb, pb, pa, pre_b, pre_a);
+    step(max_tag, diag_tag, fuse_tag, i + 2, k_lds0, v_lds2, v_lds3, sb, sa, pa, pb, pre_a, pre_b);
+    step(max_tag, diag_tag, fuse_tag, i + 3, k_lds1, v_lds3, v_lds0, sa, sb, pb, pa, pre_b, pre_a);
   };
 
   // Iterations 1 .. n_main - 1 see only tiles below the diagonal: four per loop trip,
-  // unmasked, with every slot a compile-time array and no branch inside.  The rest (up to
+  // unmasked, with every slot a compile-time array and no branch inside a step.  The rest (up to
   // three iterations left over by the four-way loop, and the tiles that cross the
   // diagonal, a few per item) run through the masked copy of the step, in the same slot
   // rotation.  (Choosing between a masked and an unmasked copy inside one step splits the
@@ -774,24 +795,32 @@ void extend_attn_kernel(ExtendArgs a) {
   // With the fused append, the steps that stream only tiles below the prefix (K(i+5) under
   // P) run a copy of the step without the fused loads, so the long walk over the cached
   // history is the plain kernel's loop.
-  const std::false_type plain, unmasked;
-  const std::true_type masked;
+  const std::false_type plain, unmasked, checked;
+  const std::true_type masked, max_first;
   const int n_main = max(1, min(ntiles, n_full - tbase));
   int i = 1;
+  // Tiles up to `end`, four a trip; the maxima come first while `hot`.  Every wave of the
+  // workgroup meets the same barriers either way.
+  auto walk = [&](auto fuse_tag, int end) __attribute__((always_inline)) {
+    while (i + 4 <= end) {
+      for (; i + 4 <= end && hot <= 0; i += 4) four(checked, unmasked, fuse_tag, i);
+      for (; i + 4 <= end && hot > 0; i += 4) four(max_first, unmasked, fuse_tag, i);
+    }
+  };
   if constexpr (kAppend) {
     const int first_new = P / 64 - tbase;  // first local tile holding a key >= P
     // a trip i .. i+3 is plain when its last stream, K(i+8), is still below first_new
     const int n_plain = min(n_main, first_new - 5);
-    for (; i + 4 <= n_plain; i += 4) four(unmasked, plain, i);
+    walk(plain, n_plain);
   }
-  for (; i + 4 <= n_main; i += 4) four(unmasked, fuse, i);
-  for (; i + 4 <= ntiles; i += 4) four(masked, fuse, i);
+  walk(fuse, n_main);
+  for (; i + 4 <= ntiles; i += 4) four(checked, masked, fuse, i);
   if (i < ntiles) {
-    step(masked, fuse, i, k_lds2, v_lds0, v_lds1, sb, sa, pa, pb, pre_a, pre_b);
+    step(checked, masked, fuse, i, k_lds2, v_lds0, v_lds1, sb, sa, pa, pb, pre_a, pre_b);
     if (i + 1 < ntiles) {
-      step(masked, fuse, i + 1, k_lds3, v_lds1, v_lds2, sa, sb, pb, pa, pre_b, pre_a);
+      step(checked, masked, fuse, i + 1, k_lds3, v_lds1, v_lds2, sa, sb, pb, pa, pre_b, pre_a);
       if (i + 2 < ntiles)
-        step(masked, fuse, i + 2, k_lds0, v_lds2, v_lds3, sb, sa, pa, pb, pre_a, pre_b);
+        step(checked, masked, fuse, i + 2, k_lds0, v_lds2, v_lds3, sb, sa, pa, pb, pre_a, pre_b);
     }
   }
   // P.V of the last tile n-1: V slot (n-1) mod 4, probabilities pa for even n-1

@@ -21,9 +21,8 @@ constexpr float kLog2e = 1.44269504088896340736f;
 // Running-max sentinel: finite so that exp2(m_old - m_new) never sees (-inf) - (-inf).
 constexpr float kNoMax = -1.0e30f;
 // A row's reference max is only raised when the tile max exceeds it by more than this
-// (base-2 units; the extend kernel raises it at weight sums of 2^8, kTileSumMax).
-// Unnormalised weights then stay <= 2^8, far from fp32/bf16 limits, and the accumulator
-// rescale is skipped on almost every tile.
+// (base-2 units).  Unnormalised weights then stay <= 2^8, far from fp32/bf16 limits,
+// and the accumulator rescale is skipped on almost every tile.
 constexpr float kRescaleSlack = 8.0f;
 
 typedef const __attribute__((address_space(4))) int32_t const_i32;

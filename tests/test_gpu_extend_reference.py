@@ -1,7 +1,7 @@
 """Rows whose score scale jumps after their first key tile (needs an MI355X).
 
 The extend kernel takes a row's softmax reference from its first 64-key tile and raises it
-only when a later tile's weights outgrow it.  Here single keys of later tiles are
+only when a later tile outgrows it.  Here single keys of later tiles are
 scaled so that the scores jump by hundreds (base 2), up and down, in some rows of a wave and
 not in others: in unmasked tiles, on the diagonal, in the first and later chunks of a
 split-KV call, and through the fused append.  A softmax over such scores is close to one-hot
@@ -90,6 +90,29 @@ def test_large_values_stay_finite(d, split, monkeypatch):
     kv.v_pool.mul_(2.0 ** 106)
     out = kv.extend_append(q, kn, vn * 2.0 ** 106, [p], [e])
     assert_close(out.double() * 2.0 ** -106, ref, "large values")
+
+
+@pytest.mark.parametrize("split", ["0", "1"])
+def test_rows_do_not_depend_on_their_wave(split, monkeypatch):
+    """A wave takes tiles' maxima before or after their weights, as its rows need.  Rows whose
+    references are raised in many tiles, and rows whose are never, give the same bits whatever
+    the rows between them are."""
+    monkeypatch.setenv("TIDE_EXTEND_SPLIT", split)
+    p, e = 2000, 64
+    scaled = {70 + 61 * i: 4.0 + i for i in range(30)}  # growing outliers
+    kv, q, kn, vn, ref, _ = build(4, 1, 128, p, e, scaled, seed=11)
+    check_plan(kv, p, e, split)
+    out = kv.extend_append(q, kn, vn, [p], [e])
+    assert_close(out, ref, "growing outliers")
+    for calm in (slice(0, None, 2), slice(1, None, 2), slice(0, None, 7)):
+        other = q.clone()
+        other[calm] *= 0.01  # their scores stay within the slack
+        got = kv.extend(other, [p], [e])
+        rest = torch.ones(e, dtype=torch.bool, device="cuda")
+        rest[calm] = False
+        assert torch.equal(got[rest], out[rest])
+        alone = kv.extend((q * 0.01).bfloat16(), [p], [e])
+        assert torch.equal(got[calm], alone[calm])
 
 
 @pytest.mark.parametrize("lse", [False, True])
