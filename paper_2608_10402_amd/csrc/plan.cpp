@@ -157,11 +157,13 @@ int task_lengths(int op, int32_t b, const int32_t* lens_a, const int32_t* lens_b
 //          merges (the split-K scheme of flash decoding, applied to extend blocks).
 // Splitting pays when a call has too few items to keep 256 CUs busy to the end, or a last
 // round of items that is nearly empty.  The choice compares run-time estimates of the plain
-// plan and of split plans whose chunks fill 1 .. kRounds rounds of the CUs: the items of a kv
+// plan and of split plans whose chunks fill 1/4 .. 6 rounds of the CUs: the items of a kv
 // head are dealt out longest first, a round of 256 / Hkv at a time, and a round lasts as long
 // as its longest item; a tile costs less while CUs are idle (the card is power-limited, so
 // its clock is higher then), a chunk costs the write of its partial, and a split plan the
-// merge.  The planner runs on every call, so a number of rounds costs one pass over the blocks
+// merge (of very many chunks, the time a row's merge takes to walk them: one task of 40,000 + 8
+// tokens at 8 / 2 heads, d = 64, takes 41 us as 124 chunks a kv head and 29 as 32).  The planner
+// runs on every call, so a number of rounds costs one pass over the blocks
 // for its estimate and about 2 log2 of the longest block's tiles for its chunk length, and only
 // the chosen plan is materialised.
 namespace {
@@ -180,11 +182,16 @@ constexpr double kItemUs = 1.0;            // first-tile latency and epilogue
 constexpr double kChunkUs = 3.0;           // the same with the partial's statistics
 constexpr double kChunkRowsUs = 6.6;       // write of 256 rows' partials, all CUs at once
 constexpr double kMergeBytesPerUs = 6.5e6; // rate at which the merge reads the partials
+constexpr double kMergePartUs = 0.26;      // the least it takes a row's merge per chunk
 constexpr double kMergeLaunchUs = 4.0;     // second kernel launch
 constexpr double kSplitGain = 0.96;        // split when estimated at least this much faster
 constexpr int kMinChunkTiles = 4;
 constexpr int kMaxChunks = 512;
-constexpr int kRounds = 6;
+// Rounds of chunks tried, in quarters.  Fewer than a round only where a block may have over
+// kManyChunks chunks: there the walk of its merge is what they cost, and with fewer the estimates
+// are too close to tell (5 tasks of 500 + 100 tokens took 31.8 us so and 30.6 unsplit).
+constexpr int kManyChunks = 32;
+constexpr int kQuarterRounds[] = {1, 2, 4, 8, 12, 16, 20, 24};
 constexpr int64_t kSplitMaxItems = 2048;  // larger calls fill the chip with the plain plan
 
 struct Block {
@@ -229,6 +236,7 @@ double estimate(const std::vector<Block>& blocks, int32_t longest, const tide_di
   std::fill_n(count, bins, 0);
   std::fill_n(most_rows, bins, 0);
   int64_t slots = 0, items = 0;
+  int32_t parts = 1;  // the most chunks of a block
   for (const Block& b : blocks) {
     if (T <= 0 || b.ntiles <= T) {  // one chunk
       ++items;
@@ -238,6 +246,7 @@ double estimate(const std::vector<Block>& blocks, int32_t longest, const tide_di
     const int32_t n = num_chunks(b.ntiles, T);
     slots += (int64_t)b.ntok * n;
     items += n;
+    parts = std::max(parts, n);
     const int32_t q = b.ntiles / n, r = b.ntiles % n, rows = b.ntok * group;
     for (int up = 0; up < 2; ++up) {
       const int32_t m = up ? r : n - r, bin = std::min(kBins - 1, (q + up) >> shift);
@@ -259,7 +268,8 @@ double estimate(const std::vector<Block>& blocks, int32_t longest, const tide_di
   }
   us *= std::max(1.0, (double)dims.num_kv_heads / kCus);
   if (slots > 0)
-    us += (double)slots * dims.num_q_heads * (dims.head_dim * 4.0 + 16.0) / kMergeBytesPerUs +
+    us += std::max((double)slots * dims.num_q_heads * (dims.head_dim * 4.0 + 16.0) / kMergeBytesPerUs,
+                   parts * kMergePartUs) +
           kMergeLaunchUs;
   *row_slots = slots;
   return us;
@@ -453,13 +463,16 @@ int plan_extend(const std::vector<TaskDesc>& tasks, const tide_dims& dims, bool 
         estimate(blocks, longest, dims, 0, tile_us, &slots);
     plan->est_plain_us = plan->est_us = plain_us;
     double best_us = mode == 1 ? INFINITY : plain_us * kSplitGain;
-    // T for 1 .. kRounds rounds: the shortest chunks that are no more than the CUs take
+    // T for each number of rounds: the shortest chunks that are no more than the CUs take
     int32_t last = -1;
     int worse = 0;
-    for (int rounds = 1; rounds <= kRounds && longest > kMinChunkTiles; ++rounds) {
-      if ((double)tiles * hkv / kCus * tile_us * (1.0 - kIdleClockGain) + rounds * kChunkUs >= best_us)
+    for (const int quarters : kQuarterRounds) {
+      if (longest <= kMinChunkTiles) break;
+      if (quarters < 4 && longest <= kManyChunks * kMinChunkTiles) continue;
+      if ((double)tiles * hkv / kCus * tile_us * (1.0 - kIdleClockGain) + quarters / 4 * kChunkUs >=
+          best_us)
         break;  // more rounds cannot win
-      const int64_t room = (int64_t)rounds * kCus / hkv;
+      const int64_t room = (int64_t)quarters * kCus / 4 / hkv;
       if ((int64_t)blocks.size() > room) continue;
       auto fits = [&](int32_t t) {
         ++plan->search_passes;

@@ -149,8 +149,8 @@ static int check(int op, const tide_dims& dims, const std::vector<int32_t>& pa,
     for (int64_t r = 0; r < plan.total_rows; ++r)
       if (seen[r] != Hkv) return fail("merge row seen", r, seen[r]);
   }
-  // the chunk length is the shortest of at least 4 tiles whose chunks fit 1 .. 6 rounds of the
-  // CUs, and found in a few passes a round
+  // the chunk length is the shortest of at least 4 tiles whose chunks fit 1/4, 1/2 or 1 .. 6 rounds
+  // of the CUs, and found in a few passes a round
   std::vector<int> ntiles;
   int longest = 1;
   for (int32_t b = 0; b < n; ++b)
@@ -160,20 +160,20 @@ static int check(int op, const tide_dims& dims, const std::vector<int32_t>& pa,
     }
   if (plan.split) {
     bool found = false;
-    for (int rounds = 1; rounds <= 6 && !found; ++rounds) {
+    for (const int quarters : {1, 2, 4, 8, 12, 16, 20, 24}) {
       int t = 4;
       for (;; ++t) {
         long chunks_of = 0;
         for (int k : ntiles) chunks_of += std::min(512, (k + t - 1) / t);
-        if (chunks_of <= (long)rounds * 256 / Hkv || t >= longest) break;
+        if (chunks_of <= (long)quarters * 64 / Hkv || t >= longest) break;
       }
-      found = t == plan.chunk;
+      found = found || t == plan.chunk;
     }
     if (!found) return fail("chunk length is no round's shortest", plan.chunk);
   }
   int bits = 0;
   while (longest >> bits) ++bits;
-  if (plan.search_passes > 6 * (2 * bits + 2)) return fail("search passes", plan.search_passes, bits);
+  if (plan.search_passes > 8 * (2 * bits + 2)) return fail("search passes", plan.search_passes, bits);
   printf("ok %d %d %lld %zu %.1f %.1f\n", plan.split ? 1 : 0, plan.num_items,
          (long long)plan.row_slots, plan.total_bytes, plan.est_plain_us, plan.est_us);
   return 0;

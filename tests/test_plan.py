@@ -100,6 +100,15 @@ def test_chunk_search_is_short(checker):
     assert sum(o[1] == "1" for o in out) >= 5
 
 
+def test_few_rows_take_few_chunks(checker):
+    """A block of 8 tokens over 40,000 keys is merged by waves that walk its chunks one batch after
+    the other, so it is not cut into as many as one round of the CUs holds (124 a kv head, which
+    took 41 us where 32 take 29)."""
+    lines = [_line(OP_EXTEND, hq, hkv, d, [40000], [8]) for hq, hkv, d in ((8, 2, 64), (32, 2, 64), (16, 1, 128))]
+    for o, hkv in zip(_run(checker, lines), (2, 2, 1)):
+        assert o[1] == "1" and int(o[2]) <= 64 * hkv
+
+
 def test_split_choice(checker):
     """Few long items are split; a full batch and tiny calls keep the plain plan."""
     few = _line(OP_EXTEND, 28, 4, 128, [6000], [380])
