@@ -56,7 +56,10 @@ constexpr int64_t kDecodeMinChunk = 512;
 constexpr int64_t kDecodeMaxChunk = 16384;
 constexpr int64_t kDecodeTargetItems = 4096;
 constexpr int64_t kStreamMaxSteps = 208;  // longest run of the equal-runs plan
-constexpr int64_t kStreamMergeSteps = 40;  // see make_plan_decode
+constexpr int64_t kStreamMergeSteps = 40;  // see make_plan_decode, with the next three
+constexpr double kStreamStepUs = 0.6;      // a step of a run, in workgroups of 4 waves
+constexpr double kStreamBusyStepUs = 1.0;  // and of 8
+constexpr double kStreamPartUs = 0.3;      // a part in the merge of G > 8 heads of d = 128
 // Shared-prefix decode in one round of waves: chunks of at most this length.
 constexpr int64_t kSharedRoundChunk = 1280;
 constexpr int64_t kFoldMeanSplits = 4;  // merge inside the split kernel up to this mean
@@ -744,6 +747,11 @@ int make_plan(int op, int32_t num_tasks, const int32_t* lens_a, const int32_t* l
 // where steps^2 is in proportion to the task's length.  One task of 60,000 keys (1875 steps), 32 /
 // 2 heads, d = 64: 2 steps a run 46.2 us, 3 35.5, 4 31.7, 6 27.5, 8 28.9, 16 29.3 (chunks 28.0);
 // 30,000 keys, 8 / 2 heads: 1 step 24.1, 2 17.5, 4 16.3, 6 18.4, 12 19.7 (chunks 24.1).
+// Over 8 query heads a kv head of d = 128 take the merging wave two passes of twice the loads, and
+// there the steps are those for which a run's steps and the parts of the longest task cost least
+// (8 waves of a workgroup share a CU and so a step costs more, but make one part): 16 / 1 heads, one
+// task of 30,000 keys 40.6 us with the rule above (4 steps) and 31.9 so (10), 9,000 27.2 (2) and
+// 21.4 (6), 2 of 90,000 62.3 (9) and 59.9 (12); no slower than 2% on 27 other calls.
 int make_plan_decode(int32_t num_tasks, const int32_t* kv_lens, const tide_dims& dims,
                      int32_t num_splits, int32_t bt_stride, bool build_blob, Plan* plan) {
   if (!plan || num_tasks < 0 || num_splits < 0) return TIDE_ERR_INVALID_ARG;
@@ -762,7 +770,20 @@ int make_plan_decode(int32_t num_tasks, const int32_t* kv_lens, const tide_dims&
   }
   const int32_t hkv = dims.num_kv_heads;
   int64_t steps = ceil_div(total, std::max<int64_t>(1, kDecodeWaveSlots / hkv));
-  while (kStreamMergeSteps * (steps + 1) * (steps + 1) <= longest) ++steps;
+  const int32_t group = dims.num_q_heads / hkv;
+  if (group > 8 && dims.head_dim > 64) {
+    int64_t best = steps;
+    double best_us = INFINITY;
+    for (int64_t s = steps; s <= kStreamMaxSteps && s * kStreamStepUs < best_us; ++s) {
+      const int32_t waves = stream_waves(ceil_div(total, s) * hkv);
+      const double us = s * (waves > 4 ? kStreamBusyStepUs : kStreamStepUs) +
+                        ceil_div(ceil_div(longest, s), waves) * kStreamPartUs;
+      if (us < best_us) best_us = us, best = s;
+    }
+    steps = best;
+  } else {
+    while (kStreamMergeSteps * (steps + 1) * (steps + 1) <= longest) ++steps;
+  }
   if (steps > kStreamMaxSteps)
     return make_plan(TIDE_OP_DECODE, num_tasks, kv_lens, nullptr, dims, num_splits, bt_stride,
                      build_blob, plan);

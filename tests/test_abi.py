@@ -345,6 +345,11 @@ def test_plan_info_matches_workspace_size_and_launch_rules():
     for keys, steps in ((5000, 157), (10000, 0)):
         info = tide.tide_plan_info_get(tide.TIDE_OP_DECODE, np.asarray([keys] * 256, np.int32), None, dims)
         assert info["run_steps"] == steps
+    # a lone task's runs are longer where its merge costs more: 938 steps, by query heads a kv head
+    for hq, hkv, d, steps in ((16, 2, 64, 4), (16, 1, 64, 4), (16, 1, 128, 10), (8, 1, 128, 4)):
+        info = tide.tide_plan_info_get(tide.TIDE_OP_DECODE, np.asarray([30000], np.int32), None,
+                                       tide.make_dims(hq, hkv, d, 0.1))
+        assert info["run_steps"] == steps
     # 40 splits asked: chunks of ceil(9000 / 40) keys rounded up to 32 -> 256 -> 36 splits
     assert many["max_splits"] == 36 and many["merge_in_kernel"] == 0
     p, e = np.asarray([1000, 20], np.int32), np.asarray([300, 5], np.int32)
