@@ -11,15 +11,17 @@
 //   * a task that begins and ends inside a run is finished by its wave.  A task cut by a
 //     run's end leaves partials (o, m, l);
 //   * the waves of a workgroup take consecutive runs, so the partials of a long context are
-//     first combined in LDS, and only one per workgroup travels through memory.  The last of
-//     a task's parts to arrive (a counter per kv head and task) merges them all, in key order.
-//     There is no merge kernel, and a call with fewer steps than waves runs one step a wave.
+//     first combined in LDS, and only one per workgroup travels through memory.  Each part then
+//     sets the flag of its slot to the call's own number, and a part that finds all flags of its
+//     task set merges the parts, in key order; should two find them, both write the same rows
+//     (`arrive`).  There is no merge kernel, and a call with fewer steps than waves runs one step
+//     a wave.
 // The step itself (K through LDS, V transposed in LDS, the G query heads as MFMA columns, the
 // cache policy) is that of attn_decode.hip; the newest token of the fused append replaces its
 // slot's row in the operands instead of being stored and waited for first.
 // Measured against the chunks (MI355X, append fused, call us; 28 / 4 heads, d = 128): 8 tasks
 // of 0.6k-3k keys 29.6 -> 24.6, 16 of 2k-16k 71.8 -> 53.3, 64 of 2k-16k 191 -> 183, 175 of
-// 0.5k-3k 132 -> 109; 32 / 8 heads: 1024 of 64-512 keys 288 -> 218, 128 of 4k-14k 743 -> 690
+// 0.5k-3k 132 -> 106; 32 / 8 heads: 1024 of 64-512 keys 288 -> 218, 128 of 4k-14k 743 -> 690
 // (6.7 TB/s).  All of the heads of one run in a workgroup instead of 8 runs of one head was
 // slower everywhere (no partials to combine in LDS), and fewer or more waves than the device
 // holds at once 2-50% slower.

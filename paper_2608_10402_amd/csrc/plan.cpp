@@ -44,10 +44,10 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // fewer than 4 chunks per unit, most items are units' shorter last chunks of scattered
 // lengths; many items then balance the launch better, and the chunk is
 // sum(kv) * Hkv / 4096 keys.  Chunks are multiples of the kernel step within [512, 16384].
-// Measured on MI355X over 15 shapes (8-1024 tasks, 0.6k-60k keys, 2-8 kv heads, GQA
-// 4:1 to 8:1): the round rule is 8-11% faster on agent_resume_7b, multimodal_resume,
-// long_horizon and the prune resume than about 4096 items, and 5% slower on
-// resumed_decode (2 chunks per unit), where the item count rule stays.
+// The rule now serves the calls whose runs would be too long (make_plan_decode).  Measured on
+// MI355X against about 4096 items, call us: 32 tasks of 32k-96k keys (64 / 8 heads) 1368 ->
+// 1242; 256 tasks of 1k-32k (32 / 8; 2 chunks per unit) 5% slower, so the item count rule
+// stays there.
 constexpr int64_t kDecodeWaveSlots = 2048;
 constexpr int64_t kDecodeRoundCost = 1200;  // keys
 constexpr int64_t kDecodeMinUnitChunks = 4;

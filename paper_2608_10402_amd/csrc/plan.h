@@ -1,6 +1,6 @@
-// Host-side planning for the four entry points: argument validation, workspace layout
-// and the per-call work lists.  Plain C++ (no HIP); the entry points in tide_api.hip
-// upload the blob it builds with one host-to-device copy.
+// Host-side planning for the entry points: argument validation, workspace layout and the
+// per-call work lists.  Plain C++ (no HIP); the entry points in tide_api.hip stage the blob
+// it builds.
 #pragma once
 
 #include <stddef.h>
@@ -24,8 +24,10 @@ struct Plan {
   // extend split-KV plan: per-row merge descriptors (uploaded after the items)
   bool split = false;
   size_t merge_rows_off = 0;
-  // decode: per-(task, kv head) arrival counters, zeros in the uploaded blob, used when
-  // the split kernel merges (fold_merge: few splits per task) instead of a merge kernel
+  // decode, at the blob's end, zeros in it.  Chunks: arrival counters per (task, kv head), used
+  // when the split kernel merges (fold_merge: few splits per task) instead of a merge kernel.
+  // Runs (`stream`): a flag per partial slot, set to the call's own number, so the zeros do not
+  // matter where the plan is read in place and never copied.
   size_t tickets_off = 0;
   bool fold_merge = false;
   // decode with the library's own split (make_plan_decode): StreamItems, one per run

@@ -184,8 +184,13 @@ struct Staged {
 // A plan that at most this many workgroups read, once each, is read where it was staged: a
 // record costs each a read of host memory (about 2 us), which is less than the copy kernel,
 // its launch and the gap behind it (3-5 us on the GPU and 3 on the host): a four-task decode
-// step went from 16.0 to 13.5 us, the smallest append + extend from 31 to 25.
+// step went from 16.0 to 13.5 us, the smallest append + extend from 31 to 25.  Each workgroup
+// pays for its own read, so the gain ends where an extend's workgroups come in rounds of the
+// CUs: copied and in place, us a call (28 / 4 heads, d = 128), extends of 64 workgroups 18.5 and
+// 16.5, 256 23.5 and 20.9, 512 38.3 and 38.9, 1,024 69.5 and 79, 2,000 134 and 145; appends of 512
+// 20.8 and 18.3, 1,024 21.4 and 18.4; decodes (up to 256 workgroups at 4 kv heads) 2 us less.
 constexpr uint32_t kInPlaceGroups = 512;
+static_assert(kStagingMin / kCopyBytesPerBlock >= kInPlaceGroups, "every slot has a flag for each");
 
 bool capturing(hipStream_t stream) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;

@@ -76,18 +76,19 @@ __device__ __forceinline__ void plan_read(const PlanReads& r, uint32_t group) {
 }
 
 // Merge of split partials, the split-K merge of flash decoding.  D / 4 lanes combine the n
-// partials of one (row, query head), so a wave takes 64 / (D / 4) of them (kMergeRows): partial s holds, at
-// ml + s * ml_stride, its running max m_s (base-2 units), the sum of its bf16-rounded weights
-// and their exact fp32 sum, and at po + s * po_stride its unnormalised output.  With M = max
-// m_s and w_s = 2^(m_s - M) the row is sum_s w_s o_s / sum_s w_s l_s, written as bf16 to orow;
-// when lse_out is non-null it receives ln(sum_s w_s l_exact_s) + M ln 2.  Every sum runs in
-// split order.  n may differ between the lanes of a wave (n < 1: nothing to do).
+// partials of one (row, query head), so a wave takes 64 / (D / 4) of them (kMergeRows):
+// partial s holds, at ml + s * ml_stride, its running max m_s (base-2 units), the sum of its
+// bf16-rounded weights and their exact fp32 sum, and at po + s * po_stride its unnormalised
+// output.  With M = max m_s and w_s = 2^(m_s - M) the row is sum_s w_s o_s / sum_s w_s l_s,
+// written as bf16 to orow; when lse_out is non-null it receives ln(sum_s w_s l_exact_s) +
+// M ln 2.  Every sum runs in split order.  n may differ between the lanes of a wave (n < 1:
+// nothing to do).
 //
 // Each lane loads the statistics and 16 bytes of 8 partials (4, where no row of the wave has
-// more) before any arithmetic, so up to 8 splits cost one memory round trip.  The merge is bound by the waves it
-// keeps in flight: with one row a wave and 8 bytes a lane (104 VGPRs, 16 waves a CU) 22,428
-// rows of 8 partials took 31.0 us, now 17.5; 8,192 rows of 3-8 partials 12.0 us, now 6.3;
-// 2,048 rows of 5-12 partials 7.8 us, now 4.9.
+// more) before any arithmetic, so up to 8 splits cost one memory round trip.  The merge is
+// bound by the waves it keeps in flight: with one row a wave and 8 bytes a lane (104 VGPRs,
+// 16 waves a CU) 22,428 rows of 8 partials took 31.0 us, now 17.5; 8,192 rows of 3-8 partials
+// 12.0 us, now 6.3; 2,048 rows of 5-12 partials 7.8 us, now 4.9.
 template <int D>
 constexpr int kMergeRows = 64 / (D / 4);
 

@@ -1,8 +1,8 @@
 """Reuse of the pinned staging slots that carry each call's work list (needs an MI355X).
 
-A call reuses one of the library's 16 staging slots only after the previous copy out of
-it has read it: each copy workgroup sets a flag that the host checks, waiting a bounded
-time and then synchronising the device.  Here a spin kernel holds the stream while 40
+A call reuses one of the library's 16 staging slots only after its last reader (the call's
+own kernel, or a copy kernel) has read it: each of the reader's workgroups sets a flag that
+the host checks, waiting a bounded time and then synchronising the device.  Here a spin kernel holds the stream while 40
 calls are queued behind it, so from the 17th call on every slot the host wants is still
 unread; with TIDE_STAGING_WAIT_US=0 each such reuse takes the fallback at once.  Every
 result must equal, bit for bit, the same call made on an idle device."""

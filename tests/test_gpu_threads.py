@@ -3,7 +3,7 @@
 Each thread has its own stream (default priority, as every stream here) and its own
 workspaces, and runs extend, decode and an append into its own copy of the pool, 12
 times over.  The library's only shared host state, the pinned staging ring, is guarded
-by a mutex, and a work list is reused only after its copy completed; so every result
+by a mutex, and a slot is reused only after its work list was read; so every result
 must equal, bit for bit, the same call made alone on the default stream."""
 import threading
 
