@@ -74,9 +74,9 @@ PROFILE_SUMMARIES = {
     ("multimodal_resume", "extend"): "attn_extend_multimodal_resume_counters.txt",
     ("long_horizon", "extend"): "attn_extend_long_horizon_counters.txt",
     ("long_horizon", "decode"): "decode_split_long_horizon_counters.txt",
-    ("agent_resume_7b", "decode"): "decode_split_agent_resume_7b_counters.txt",
-    ("multimodal_resume", "decode"): "decode_split_multimodal_resume_counters.txt",
-    ("multimodal_prune_resume", "decode"): "decode_split_multimodal_prune_resume_counters.txt",
+    ("agent_resume_7b", "decode"): "decode_stream_agent_resume_7b_counters.txt",
+    ("multimodal_resume", "decode"): "decode_stream_multimodal_resume_counters.txt",
+    ("multimodal_prune_resume", "decode"): "decode_stream_multimodal_prune_resume_counters.txt",
 }
 
 
@@ -557,7 +557,7 @@ def run_ctb(args, torch, tide):
     ctb = res["ctb"]
     v = ctb["decode_GBps"]
     roofline = {"bound": "hbm", "achieved": v, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                "frac": round(v / PEAK_HBM_GBS, 4), "kernel": "decode_split_kernel<128, false, true, 4|8>",
+                "frac": round(v / PEAK_HBM_GBS, 4), "kernel": "decode_stream_kernel<128, true, 4|8>",
                 "traffic": None}
     extra = {"policies": res, "setup_s": round(setup_s, 1),
              "attention_speedup_ctb_vs_request_f1024": round(
