@@ -831,6 +831,22 @@ int make_plan_decode(int32_t num_tasks, const int32_t* kv_lens, const tide_dims&
   return TIDE_OK;
 }
 
+size_t compact_runs(Plan* plan) {
+  TaskDesc* tasks = reinterpret_cast<TaskDesc*>(plan->blob.data() + plan->tasks_off);
+  uint8_t* to = plan->blob.data() + plan->items_off;
+  const StreamItem* items = reinterpret_cast<const StreamItem*>(to);
+  int32_t at = 0;
+  for (int32_t b = 0; b < plan->num_tasks; ++b) {
+    tasks[b].aux = at;
+    at += (tasks[b].prefix + kDecodeStep) / kDecodeStep;
+  }
+  for (int32_t r = 0; r < plan->num_runs; ++r) {  // (never past the record it reads)
+    const int32_t task = items[r].task;
+    memcpy(to + r * sizeof(int32_t), &task, sizeof(int32_t));
+  }
+  return plan->items_off + plan->num_runs * sizeof(int32_t);
+}
+
 int make_plan_shared(int32_t num_tasks, const int32_t* kv_lens, int32_t num_groups,
                      const int32_t* group_start, const int32_t* shared_lens,
                      const tide_dims& dims, int32_t num_splits, int32_t bt_stride,

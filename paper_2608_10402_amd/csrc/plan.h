@@ -71,6 +71,11 @@ int make_plan(int op, int32_t num_tasks, const int32_t* lens_a, const int32_t* l
 int make_plan_decode(int32_t num_tasks, const int32_t* kv_lens, const tide_dims& dims,
                      int32_t num_splits, int32_t bt_stride, bool build_blob, Plan* plan);
 
+// The runs of a decode plan as one int32 each, the task a run starts in, in place of the
+// StreamItems; the task table then holds each task's first step (aux), from which the rest
+// follows.  Returns the bytes of the blob up to their end.
+size_t compact_runs(Plan* plan);
+
 // Shared-prefix decode: groups are consecutive task ranges [group_start[g],
 // group_start[g+1]); the first shared_lens[g] keys (a multiple of the page size, below
 // every member's kv_len) live in pages every member's block table shares.

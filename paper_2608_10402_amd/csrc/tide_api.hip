@@ -385,12 +385,16 @@ int run_decode(const void* q, const void* k_new, const void* v_new, const void* 
     rc = scratch_address(&workspace);
     if (rc != TIDE_OK) return rc;
     // the blob starts with the zeroed header, so this also clears the error flags; a captured
-    // copy would read the plan's host buffer at every replay, long after it is freed
+    // copy would read the plan's host buffer at every replay, long after it is freed.  A copy
+    // from pageable memory takes 9 us up to 16 KB and 18 beyond, so the runs go as 4 bytes each
+    // (64 tasks of 2,000 keys, 8 / 2 heads, d = 64: 22 KB and 33 us a call, now 5 KB and 19.5;
+    // as chunks 24), and the flags not at all.
+    const size_t bytes = plan.stream ? compact_runs(&plan) : plan.blob.size();
     if (capturing(s)) {
       rc = put_plan(plan, workspace, s);
       if (rc != TIDE_OK) return rc;
-    } else if (hipMemcpyAsync(workspace, plan.blob.data(), plan.blob.size(), hipMemcpyHostToDevice,
-                              s) != hipSuccess) {
+    } else if (hipMemcpyAsync(workspace, plan.blob.data(), bytes, hipMemcpyHostToDevice, s) !=
+               hipSuccess) {
       return TIDE_ERR_HIP;
     }
     st.plan = static_cast<const uint8_t*>(workspace);
@@ -423,6 +427,7 @@ int run_decode(const void* q, const void* k_new, const void* v_new, const void* 
     a.last_steps = plan.last_steps;
     a.tasks = at<TaskDesc>(st.plan, plan.tasks_off);
     a.items = at<StreamItem>(st.plan, plan.items_off);
+    a.item_bytes = in_scratch ? sizeof(int32_t) : sizeof(StreamItem);
     a.reads = st.reads;
     a.part_o = at_mut<float>(workspace, plan.part_o_off);
     a.part_ml = at_mut<float>(workspace, plan.part_ml_off);

@@ -288,6 +288,7 @@ struct StreamArgs {
   int32_t last_steps;  // steps of the last run, 1 .. steps
   const TaskDesc* tasks;  // prefix + extend == kv_len
   const StreamItem* items;
+  int32_t item_bytes;  // from one to the next: of a StreamItem, or 4 (compact_runs)
   int32_t num_tasks;
   // partials: per kv head the slots of StreamSlots
   float* part_o;     // [Hkv][slots][group][d] unnormalised outputs

@@ -6,7 +6,8 @@
 //   * every cut task's parts, as each of its waves derives them, agree; the slots written
 //     are distinct, in bounds, the ones the merge reads, and in key order; and as many parts
 //     are flagged as the merge waits for;
-//   * the workspace regions lie in order, the flags zero in the upload.
+//   * the workspace regions lie in order, the flags zero in the upload;
+//   * the compact form of the runs (compact_runs) names the same ones.
 #include <stdio.h>
 
 #include <algorithm>
@@ -124,6 +125,16 @@ static int check(const tide_dims& dims, const std::vector<int32_t>& kv) {
       if (f->second <= last) return fail("part order in the merge", e);
       last = f->second;
     }
+  }
+  // the compact form names the same runs
+  const std::vector<StreamItem> full(items, items + R);
+  const size_t bytes = compact_runs(&plan);
+  if (bytes != plan.items_off + R * 4 || bytes > plan.blob.size()) return fail("compact bytes", (long)bytes);
+  for (size_t r = 0; r < R; ++r) {
+    const int32_t t = reinterpret_cast<const int32_t*>(plan.blob.data() + plan.items_off)[r];
+    if (t != full[r].task || (int)r * plan.steps - tasks[t].aux != full[r].step ||
+        tasks[t].prefix + tasks[t].extend != full[r].kv_len)
+      return fail("compact run", (long)r);
   }
   printf("ok %d %d %zu\n", plan.num_items, plan.steps, cut.size());
   return 0;

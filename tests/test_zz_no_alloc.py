@@ -24,6 +24,8 @@ CASES = [
     ("small_g4_d128", lambda: W.custom_workload(16, 4, 128, [0, 15, 16, 31, 300], [1] * 5,
                                                 seed=31), 0),
     ("resumed_decode/4 again", lambda: W.make_workload(S["resumed_decode"].shrunk(64, 4)), 3),
+    ("over_1024_runs", lambda: W.custom_workload(8, 1, 64, [500 + 31 * i for i in range(64)], [1] * 64,
+                                                 seed=33), 0),
     ("small_g16_d64", lambda: W.custom_workload(16, 1, 64, [7, 100, 2047], [1] * 3, seed=32), 0),
 ]
 
